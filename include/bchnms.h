@@ -163,8 +163,10 @@ enum {
     BCH_DEC_SMALL_ALWAYS = 4,  /* N = 127: always use the small-batch kernel (the nine
                                   branches of 64 frames on three waves) where registered */
     BCH_DEC_SMALL_NEVER = 8,   /* N = 127: never use it.  Without either flag a decode of at
-                                  most 128 frames per CU uses it, a larger one the kernel
-                                  of one wave per 64 frames; the results are the same.
+                                  most 128 frames per CU runs the row-parallel kernel, a
+                                  larger one the kernel of one wave per 64 frames; either
+                                  flag also excludes the row-parallel kernel (both code
+                                  lengths); the results are the same.
                                   Both flags together, or any other bit, give BCH_EINVAL */
     BCH_DEC_UNPACKED16 = 16,   /* BCH_FIX8: never the packed 16-bit kernel (with
                                   BCH_DEC_PACKED16: BCH_EINVAL) */
@@ -198,9 +200,14 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
                        bch_decoder *out);
 /* 1 if the decoder runs a PCM-specialised kernel, 0 for the generic one. */
 int bch_decoder_is_specialized(bch_decoder dec);
-/* Name of the kernel a decode of F frames runs ("generic" for the generic
- * kernel, "" for a null decoder); the string is static and owned by the
- * library. */
+/* Name of the kernel registered for a decode of F frames ("generic" for the
+ * generic kernel, "" for a null decoder); the string is static and owned by
+ * the library.  Nine-branch restart-mode decoders without BCH_DEC_PACKED16,
+ * BCH_DEC_SMALL_ALWAYS or BCH_DEC_SMALL_NEVER run small calls (N = 127: up to
+ * 128 frames per CU, N = 63: 224, a mixed-code call without either of its
+ * flags: 256) on the row-parallel kernel instead, a frame per workgroup in one
+ * launch, with the same results bit for bit; the name is that of the
+ * lane-per-frame kernel it stands in for. */
 const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F);
 void bch_decoder_destroy(bch_decoder dec);
 
@@ -244,7 +251,7 @@ int bch_nms_decode_batch_noalloc(bch_decoder dec, const void *llr, int64_t ld, i
  * persistent grid (0: the kernel's default; the nine-branch N = 63 kernels
  * run workgroups of three waves, so waves_per_cu / 3 of them per CU).  A
  * decode of F frames never launches more than its frames can occupy.  No
- * effect on the generic kernel.  Not thread-safe against a concurrent
+ * effect on the generic and the row-parallel kernel.  Not thread-safe against a concurrent
  * decode. */
 int bch_decoder_set_tuning(bch_decoder dec, int waves_per_cu);
 
@@ -265,7 +272,10 @@ int bch_decoder_set_tuning(bch_decoder dec, int waves_per_cu);
  * over: one launch saves the per-code launch tails, which dominate small
  * batches, while at large batches each code's own kernel is faster (the
  * 63-bit codes' kernels run three waves per SIMD, the mixed kernel one, and
- * large fixed-point calls take the packed 16-bit kernels).  No host synchronisation, no memset: the call
+ * large fixed-point calls take the packed 16-bit kernels).  Calls of at most
+ * 256 frames per CU run the row-parallel kernel (bch_decoder_kernel_name) in
+ * one launch of any codes, unless a decoder has one of those two flags or
+ * excludes it.  No host synchronisation, no memset: the call
  * can be captured in a HIP graph and replayed.  Per-frame results do not
  * depend on the mix or the path: each frame decodes exactly as alone.
  */
@@ -277,9 +287,10 @@ int bch_mixed_decode_batch(const bch_decoder *decs, int n_codes, const uint8_t *
                            uint8_t *iters, uint8_t *flags, void *workspace, size_t ws_bytes,
                            hipStream_t stream);
 
-/* Name of the kernel a mixed call of F frames over decs[0..n_codes) runs:
- * the mixed-code kernel's, or "per-code" ("" for bad arguments); static,
- * owned by the library. */
+/* Name of the kernel registered for a mixed call of F frames over
+ * decs[0..n_codes): the mixed-code kernel's, or "per-code" ("" for bad
+ * arguments); static, owned by the library.  Small calls run the row-parallel
+ * kernel in its place (bch_decoder_kernel_name). */
 const char *bch_mixed_kernel_name(const bch_decoder *decs, int n_codes, int64_t F);
 
 /* Syndrome test of eq. 5 with the code's standard PCM: ok[f] = 1 iff

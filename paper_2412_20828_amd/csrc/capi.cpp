@@ -12,6 +12,7 @@
 #include "internal.h"
 #include "kernels.h"
 #include "philox.h"
+#include "rowpar.h"
 #include "spec_registry.h"
 
 struct bch_code_s {
@@ -35,6 +36,8 @@ struct bch_decoder_s {
     const bch::SpecKernel *spec_small = nullptr;  // small-batch kernel (N = 127), or null
     const bch::SpecKernel *spec_packed = nullptr; // fixed point: packed 16-bit kernel for large calls, or null
     uint64_t fingerprint = 0;                     // of the matrix (mixed-code kernel lookup)
+    uint8_t *d_rowpar = nullptr;                  // tables of the row-parallel kernel, or null: never use it
+    bch::RowParTab rowpar{};
 };
 
 namespace bch {
@@ -109,7 +112,8 @@ static int waves_of(const bch_decoder_s *d)
 // N = 63 (1.09x), slower at 1,000,000 frames for N = 63 (0.73x)
 static int64_t packed_min_frames(int N) { return N > 64 ? 4000000 : 8000000; }
 
-// the kernel of a decode of F frames: the small-batch kernel (three waves per
+// the lane-per-frame kernel of a decode of F frames (calls that the
+// row-parallel kernel does not take): the small-batch kernel (three waves per
 // 64 frames) when it is registered and F gives each CU at most 128 frames
 // (measured on the 127-bit codes: 2.7x faster up to 64 frames per CU, 1.2x at
 // 128, 0.9x at 256), or when the decoder asks for it always; else the
@@ -189,6 +193,79 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
     return e == hipSuccess ? BCH_OK : hip_fail(e, "specialised kernel launch");
 }
 
+// Largest call of the row-parallel kernel (k_rowpar.hip), whose time grows with
+// the frame-iterations from the first frame on; the lane-per-frame kernels
+// take the time of their slowest frame's iterations up to about 64 frames per
+// CU and stop early only frame by frame.  Measured in us per call, row-parallel
+// against the kernel it replaces, at 2 dB (hardest case, 3.0-7.6 iterations a
+// frame) and 3 dB, on 256 CUs:
+//   N = 127, 72 rows  16384: 711 / 773, 518 / 603   32768: 1193 / 1227, 946 / 996
+//                     40960: 1412 / 1306
+//   N = 127, 33 rows  16384: 567 / 661, 388 / 473   32768: 1031 / 1027, 737 / 814
+//   N = 63, 122 rows  32768: 650 / 939, 349 / 924   49152: 866 / 1074, 486 / 1069
+//                     65536: 1110 / 1115, 629 / 1105 (fixed point 1202 / 1169)
+//   N = 63, 33 rows   32768: 192 / 306, 122 / 300   65536: 348 / 370, 222 / 366
+// hence 128 frames per CU for N > 64 and 224 for N <= 64.  A mixed-code call of
+// the service's four codes takes 899 / 1450 us at 32768 frames, 1684 / 1731 at
+// 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455 at 65536 over 2-5 dB):
+// 256 per CU.
+static int64_t rowpar_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * (d->N > 64 ? 128 : 224); }
+static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
+
+// one launch of the row-parallel kernel: frame f with decs[code_idx[f]] (or
+// decs[0] without a code index)
+static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *code_idx, const void *llr, int64_t ld,
+                         int64_t F, const uint8_t *d_o, uint64_t *bits, int64_t bits_ld, uint8_t *iters,
+                         uint8_t *flags, void *trace, hipStream_t stream)
+{
+    RowParArgs a{};
+    a.llr = llr;
+    a.ld = ld;
+    a.F = F;
+    a.d_o = d_o;
+    a.code_idx = code_idx;
+    a.bits = bits;
+    a.bits_ld = bits_ld;
+    a.iters = iters;
+    a.flags = flags;
+    a.trace = trace;
+    a.n_codes = n_codes;
+    for (int c = 0; c < n_codes; c++)
+        a.tab[c] = decs[c]->rowpar;
+    hipError_t e = launch_rowpar(a, decs[0]->prm.precision == BCH_FIX8, stream);
+    return e == hipSuccess ? BCH_OK : hip_fail(e, "row-parallel kernel launch");
+}
+
+// device copy of a decoder's row-parallel tables
+static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
+{
+    const int dp = shift_period(d->N);
+    RowParImage im;
+    if (rowpar_lds_bytes(d->N, d->M, dp) > kRpMaxLds || !build_rowpar(p, im))
+        return hipSuccess;
+    hipError_t e = hipMalloc(&d->d_rowpar, im.data.size());
+    if (e == hipSuccess)
+        e = hipMemcpy(d->d_rowpar, im.data.data(), im.data.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess)
+        return e;
+    RowParTab &t = d->rowpar;
+    t.steps = reinterpret_cast<const uint32_t *>(d->d_rowpar + im.steps);
+    t.rounds = reinterpret_cast<const uint32_t *>(d->d_rowpar + im.rounds);
+    t.mask = reinterpret_cast<const uint4 *>(d->d_rowpar + im.mask);
+    t.slot = reinterpret_cast<const uint32_t *>(d->d_rowpar + im.slot);
+    t.recs = reinterpret_cast<const uint2 *>(d->d_rowpar + im.recs);
+    t.hsyn = d->d_hsyn;
+    t.n_rounds = im.n_rounds;
+    t.n_recs = im.n_recs;
+    t.N = d->N;
+    t.M = d->M;
+    t.dp = dp;
+    t.msyn = d->msyn;
+    t.max_iter = d->prm.max_iter;
+    t.alpha = d->prm.alpha;
+    return hipSuccess;
+}
+
 // the mixed-code kernel for decoders decs[0..n) in this order (nine-branch
 // restart-mode specialised decoders of one precision), or null
 static const bch::MixKernel *mixed_kernel_of(const bch_decoder *decs, int n, int64_t F)
@@ -255,6 +332,7 @@ static int mixed_fused(const bch::MixKernel *k, const bch_decoder *decs, int n_c
 
 using namespace bch;
 
+static_assert(BCH_MAX_MIX <= kRpMaxCodes, "codes of one row-parallel launch");
 static_assert(BCH_NOALLOC_SCRATCH_BYTES == kNoAllocScratchBytes, "scratch size of the header and the library");
 
 extern "C" {
@@ -599,6 +677,19 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
             d->spec_packed = find_spec_kernel(p, q, 1);
     }
     d->fingerprint = pcm_fingerprint(p);
+    if (d->spec && q.n_branches == 9 && q.mode == BCH_MODE_RESTART &&
+        !(q.flags & (BCH_DEC_PACKED16 | BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER))) {
+        try {
+            he = make_rowpar(d, p);
+        } catch (const std::bad_alloc &) {
+            bch_decoder_destroy(d);
+            return fail(BCH_ENOMEM, "row-parallel tables");
+        }
+        if (he != hipSuccess) {
+            bch_decoder_destroy(d);
+            return hip_fail(he, "row-parallel tables");
+        }
+    }
     if (hipDeviceGetAttribute(&d->n_cu, hipDeviceAttributeMultiprocessorCount, d->dev) != hipSuccess ||
         d->n_cu <= 0)
         d->n_cu = 256;
@@ -625,6 +716,8 @@ void bch_decoder_destroy(bch_decoder dec)
         (void)hipFree(dec->d_colp);
     if (dec->d_gen)
         (void)hipFree(dec->d_gen);
+    if (dec->d_rowpar)
+        (void)hipFree(dec->d_rowpar);
     delete dec;
 }
 
@@ -668,6 +761,8 @@ int bch_nms_decode_batch(bch_decoder dec, const void *llr, int64_t ld, int64_t F
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess || cur != dec->dev)
         return fail(BCH_EINVAL, "decoder belongs to another device");
+    if (dec->d_rowpar && F <= rowpar_max_frames(dec))
+        return rowpar_decode(&dec, 1, nullptr, llr, ld, F, d_o, bits, dec->W64, iters, flags, y_trace, stream);
     if (dec->spec)
         return spec_decode(dec, llr, ld, F, d_o, nullptr, 0, bits, dec->W64, iters, flags, y_trace, workspace,
                            stream);
@@ -779,6 +874,12 @@ int bch_mixed_decode_batch(const bch_decoder *decs, int n_codes, const uint8_t *
     const size_t need = bch_mixed_workspace_size(decs, n_codes, F);
     if (!workspace || ws_bytes < need)
         return fail(BCH_ENOMEM, "workspace too small");
+    bool rowpar = true;
+    for (int c = 0; c < n_codes; c++)
+        rowpar = rowpar && decs[c]->d_rowpar && F <= rowpar_max_mixed(decs[c]) &&
+                 !(decs[c]->prm.flags & (BCH_DEC_NO_MIXED_KERNEL | BCH_DEC_MIXED_KERNEL));
+    if (rowpar)
+        return rowpar_decode(decs, n_codes, code_idx, llr, ld, F, d_o, bits, bits_ld, iters, flags, nullptr, stream);
     if (const bch::MixKernel *k = mixed_kernel_of(decs, n_codes, F))
         return mixed_fused(k, decs, n_codes, code_idx, llr, ld, F, d_o, bits, bits_ld, iters, flags, workspace,
                            stream);

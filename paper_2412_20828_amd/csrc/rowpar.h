@@ -1,0 +1,66 @@
+// Row-parallel decoder: one workgroup per frame, lanes over the check rows and
+// then over the coordinates, every index list read from tables made once per
+// decoder.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+#include <vector>
+
+#include "internal.h"
+
+namespace bch {
+
+constexpr int kRpMaxCodes = 8;   // codes of one launch (a mixed batch)
+constexpr int kRpCols = 6;       // columns of a row per table step
+constexpr int kRpRecs = 4;       // row records of a coordinate per table step
+constexpr size_t kRpMaxLds = 65536;  // LDS of one workgroup; a larger matrix does not use the kernel
+
+// One code's tables (device pointers into one allocation) and parameters.
+struct RowParTab {
+    const uint32_t *steps;   // [step][64][3]: six 16-bit byte offsets into the extended input of a type
+    const uint32_t *rounds;  // [round]: steps of the round
+    const uint4 *mask;       // [round][64]: the row's columns as bits of the shift-0 sign word
+    const uint32_t *slot;    // [round][64]: byte offset of the row's record
+    const uint2 *recs;       // [chunk][64 NK]: four 16-bit byte offsets of row records
+    const uint64_t *hsyn;    // [msyn][ceil(N/64)] standard parity-check rows
+    int n_rounds, n_recs;        // n_recs: records of a coordinate (the longest list)
+    int N, M, dp, msyn;
+    int max_iter;
+    float alpha;
+};
+
+struct RowParArgs {
+    const void *llr;          // [F][ld] float32, or int8
+    int64_t ld;
+    int64_t F;
+    const uint8_t *d_o;       // [F]
+    const uint8_t *code_idx;  // [F] or null (every frame: tab[0])
+    uint64_t *bits;           // [F][bits_ld]
+    int64_t bits_ld;
+    uint8_t *iters;           // [F]
+    uint8_t *flags;           // [F]
+    void *trace;              // [F][max_iter][ld] float32 / int32, or null (one code only)
+    int n_codes;
+    RowParTab tab[kRpMaxCodes];
+};
+
+// Host image of a code's tables; offsets in bytes into `data`.
+struct RowParImage {
+    std::vector<uint8_t> data;
+    size_t steps = 0, rounds = 0, mask = 0, slot = 0, recs = 0;
+    int n_rounds = 0, n_recs = 0;
+};
+
+// Tables of the nine-branch restart-mode decode of matrix p; false if an
+// offset would not fit its 16 bits.
+bool build_rowpar(const Pcm &p, RowParImage &out);
+
+// LDS bytes of one workgroup on this code
+size_t rowpar_lds_bytes(int N, int M, int dp);
+
+hipError_t launch_rowpar(const RowParArgs &a, int fix8, hipStream_t stream);
+
+}  // namespace bch
