@@ -326,8 +326,8 @@ int bch_osd_decode_device(bch_decoder dec, const float *llr, int64_t ld, int64_t
 
 /* The same over a mixed-code batch (as bch_mixed_decode_batch): frame f is
  * decoded with decs[code_idx[f]]'s code unless skip[f] != 0 (skip may be
- * NULL); frames with code_idx >= n_codes are left alone.  One launch per code
- * on stream; allocates nothing. */
+ * NULL); frames with code_idx >= n_codes are left alone.  One launch on stream
+ * if every code has N - K <= 64, else one per code; allocates nothing. */
 int bch_mixed_osd_decode(const bch_decoder *decs, int n_codes, const uint8_t *code_idx, const float *llr,
                          int64_t ld, int64_t F, int order, const uint8_t *skip, uint64_t *bits, int64_t bits_ld,
                          hipStream_t stream);

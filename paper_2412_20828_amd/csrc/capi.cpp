@@ -29,6 +29,7 @@ struct bch_decoder_s {
     uint8_t *d_colp = nullptr;
     uint64_t *d_hsyn = nullptr;
     uint32_t *d_gen = nullptr;  // [K][4] generator rows (device OSD)
+    uint64_t *d_hcol = nullptr; // [N] parity-check columns (device OSD of codes with N - K <= 64), or null
     int msyn = 0;
     int n_cu = 0;
     int waves = 0;  // waves per CU of the persistent grid (0: the kernel's default)
@@ -332,6 +333,7 @@ static int mixed_fused(const bch::MixKernel *k, const bch_decoder *decs, int n_c
 
 using namespace bch;
 
+static_assert(BCH_MAX_MIX <= kOsdMaxCodes, "codes of one OSD launch");
 static_assert(BCH_MAX_MIX <= kRpMaxCodes, "codes of one row-parallel launch");
 static_assert(BCH_NOALLOC_SCRATCH_BYTES == kNoAllocScratchBytes, "scratch size of the header and the library");
 
@@ -664,6 +666,16 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
         he = hipMalloc(&d->d_gen, gen.size() * sizeof(uint32_t));
     if (he == hipSuccess)
         he = hipMemcpy(d->d_gen, gen.data(), gen.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+    if (osd_variant_of(c.N, c.K) >= 0) {
+        uint64_t hcol[128] = {0};
+        for (int b = 0; b < c.N - c.K; b++)
+            for (int i = 0; i < c.N; i++)
+                hcol[i] |= (uint64_t)c.Hstd[b].get(i) << b;
+        if (he == hipSuccess)
+            he = hipMalloc(&d->d_hcol, c.N * sizeof(uint64_t));
+        if (he == hipSuccess)
+            he = hipMemcpy(d->d_hcol, hcol, c.N * sizeof(uint64_t), hipMemcpyHostToDevice);
+    }
     if (he != hipSuccess) {
         bch_decoder_destroy(d);
         return hip_fail(he, "decoder tables");
@@ -716,6 +728,8 @@ void bch_decoder_destroy(bch_decoder dec)
         (void)hipFree(dec->d_colp);
     if (dec->d_gen)
         (void)hipFree(dec->d_gen);
+    if (dec->d_hcol)
+        (void)hipFree(dec->d_hcol);
     if (dec->d_rowpar)
         (void)hipFree(dec->d_rowpar);
     delete dec;
@@ -929,7 +943,14 @@ int bch_osd_decode_device(bch_decoder dec, const float *llr, int64_t ld, int64_t
     a.N = dec->N;
     a.K = dec->K;
     a.order = order;
-    hipError_t e = launch_osd(a, dec->n_cu, stream);
+    hipError_t e;
+    if (dec->d_hcol) {
+        a.n_codes = 1;
+        a.code[0] = OsdCode{dec->d_hcol, dec->N, dec->K, osd_variant_of(dec->N, dec->K)};
+        e = launch_osd_dual(a, dec->n_cu, stream);
+    } else {
+        e = launch_osd(a, dec->n_cu, stream);
+    }
     return e == hipSuccess ? BCH_OK : hip_fail(e, "device OSD launch");
 }
 
@@ -956,30 +977,38 @@ int bch_mixed_osd_decode(const bch_decoder *decs, int n_codes, const uint8_t *co
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess)
         return fail(BCH_EDEVICE, "hipGetDevice failed");
+    bool dual = true;
     for (int c = 0; c < n_codes; c++) {
-        const bch_decoder_s *d = decs[c];
-        if (d->dev != cur)
+        if (decs[c]->dev != cur)
             return fail(BCH_EINVAL, "decoder belongs to another device");
-        if (d->N > 128 || d->K > 128)
+        if (decs[c]->N > 128 || decs[c]->K > 128)
             return fail(BCH_EUNSUPPORTED, "device OSD needs N, K <= 128");
-        OsdArgs a{};
-        a.llr = llr;
-        a.ld = ld;
-        a.F = F;
-        a.skip = skip;
-        a.code_idx = code_idx;
-        a.code = c;
-        a.bits = bits;
-        a.bits_ld = bits_ld;
-        a.G = d->d_gen;
-        a.N = d->N;
-        a.K = d->K;
-        a.order = order;
-        hipError_t e = launch_osd(a, d->n_cu, stream);
-        if (e != hipSuccess)
-            return hip_fail(e, "device OSD launch");
+        dual = dual && decs[c]->d_hcol;
     }
-    return BCH_OK;
+    OsdArgs a{};
+    a.llr = llr;
+    a.ld = ld;
+    a.F = F;
+    a.skip = skip;
+    a.code_idx = code_idx;
+    a.bits = bits;
+    a.bits_ld = bits_ld;
+    a.order = order;
+    hipError_t e = hipSuccess;
+    if (dual) {
+        a.n_codes = n_codes;
+        for (int c = 0; c < n_codes; c++)
+            a.code[c] = OsdCode{decs[c]->d_hcol, decs[c]->N, decs[c]->K, osd_variant_of(decs[c]->N, decs[c]->K)};
+        e = launch_osd_dual(a, decs[0]->n_cu, stream);
+    }
+    for (int c = 0; c < n_codes && !dual && e == hipSuccess; c++) {
+        a.which = c;
+        a.G = decs[c]->d_gen;
+        a.N = decs[c]->N;
+        a.K = decs[c]->K;
+        e = launch_osd(a, decs[c]->n_cu, stream);
+    }
+    return e == hipSuccess ? BCH_OK : hip_fail(e, "device OSD launch");
 }
 
 int bch_syndrome_check(bch_code code, const uint64_t *bits, int64_t F, uint8_t *ok,

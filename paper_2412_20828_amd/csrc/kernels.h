@@ -46,19 +46,33 @@ hipError_t launch_draw_offsets(uint64_t seed, uint64_t key_hi, int64_t base, int
 hipError_t launch_quantize(const float *llr, int64_t ld, int64_t F, int N, float scale,
                            int8_t *q, int64_t ldq, hipStream_t stream);
 
+constexpr int kOsdMaxCodes = 8;
+
+// a code of an OSD launch by the parity side (N - K <= 64)
+struct OsdCode {
+    const uint64_t *hcol;  // [N] parity-check columns, N - K bits
+    int N, K, variant;     // variant: osd_variant_of(N, K)
+};
+
 struct OsdArgs {
     const float *llr;     // [F][ld] channel LLRs
     int64_t ld;
     int64_t F;
     const uint8_t *skip;  // [F], nonzero: leave the frame alone; or null
-    const uint8_t *code_idx;  // [F] or null: only frames with code_idx[f] == code
-    int code;
+    const uint8_t *code_idx;  // [F] or null: only frames with code_idx[f] == which
+    int which;
     uint64_t *bits;       // [F][bits_ld]
     int64_t bits_ld;
     const uint32_t *G;    // [K][4] generator rows, bit i of row k = word i / 32, bit i % 32
     int N, K, order;
     int keep_costs;       // set by launch_osd: pass-1 costs in LDS as words (1) or saturated half-words (2)
+    int n_codes;          // launch_osd_dual: codes, frame f is code[code_idx[f]]'s (code[0]'s without code_idx)
+    OsdCode code[kOsdMaxCodes];
 };
+
+// instance of the parity-side kernel for a code, -1 if there is none
+int osd_variant_of(int N, int K);
+hipError_t launch_osd_dual(const OsdArgs &a, int n_cu, hipStream_t stream);
 
 hipError_t launch_osd(const OsdArgs &a, int n_cu, hipStream_t stream);
 
