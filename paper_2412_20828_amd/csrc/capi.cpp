@@ -39,6 +39,8 @@ struct bch_decoder_s {
     uint64_t fingerprint = 0;                     // of the matrix (mixed-code kernel lookup)
     uint8_t *d_rowpar = nullptr;                  // tables of the row-parallel kernel, or null: never use it
     bch::RowParTab rowpar{};
+    uint8_t *d_rowgen = nullptr;                  // generic decoder: tables of its row-parallel kernel, or null
+    bch::RowGenTab rowgen{};
 };
 
 namespace bch {
@@ -264,6 +266,38 @@ static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
     t.msyn = d->msyn;
     t.max_iter = d->prm.max_iter;
     t.alpha = d->prm.alpha;
+    return hipSuccess;
+}
+
+// device copy of a generic decoder's row-parallel tables
+static hipError_t make_rowgen(bch_decoder_s *d, const Pcm &p)
+{
+    const bool memory = d->prm.mode != BCH_MODE_RESTART;
+    RowParImage im;
+    if (!build_rowgen(p, d->prm.n_branches, memory, im))
+        return hipSuccess;
+    RowGenTab t{};
+    t.n_rounds = im.n_rounds;
+    for (int s = 0; s < 3; s++)
+        t.seg[s] = im.seg[s];
+    t.stride = rowgen_stride(im, memory);
+    t.offsets = d->prm.n_branches > 1;
+    t.ns = t.offsets ? 3 : 1;
+    t.np = d->prm.n_branches == 9 ? 3 : 1;
+    t.dp = t.offsets ? shift_period(d->N) : 0;
+    if (rowgen_lds_bytes(t, d->N, d->M, d->prm.mode) > kRpMaxLds)
+        return hipSuccess;
+    hipError_t e = hipMalloc(&d->d_rowgen, im.data.size());
+    if (e == hipSuccess)
+        e = hipMemcpy(d->d_rowgen, im.data.data(), im.data.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess)
+        return e;
+    t.steps = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.steps);
+    t.rounds = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.rounds);
+    t.mask = reinterpret_cast<const uint4 *>(d->d_rowgen + im.mask);
+    t.slot = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.slot);
+    t.recs = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.recs);
+    d->rowgen = t;
     return hipSuccess;
 }
 
@@ -689,18 +723,19 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
             d->spec_packed = find_spec_kernel(p, q, 1);
     }
     d->fingerprint = pcm_fingerprint(p);
-    if (d->spec && q.n_branches == 9 && q.mode == BCH_MODE_RESTART &&
-        !(q.flags & (BCH_DEC_PACKED16 | BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER))) {
-        try {
+    try {
+        if (!d->spec && q.precision == BCH_FP32)
+            he = make_rowgen(d, p);
+        else if (d->spec && q.n_branches == 9 && q.mode == BCH_MODE_RESTART &&
+                 !(q.flags & (BCH_DEC_PACKED16 | BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER)))
             he = make_rowpar(d, p);
-        } catch (const std::bad_alloc &) {
-            bch_decoder_destroy(d);
-            return fail(BCH_ENOMEM, "row-parallel tables");
-        }
-        if (he != hipSuccess) {
-            bch_decoder_destroy(d);
-            return hip_fail(he, "row-parallel tables");
-        }
+    } catch (const std::bad_alloc &) {
+        bch_decoder_destroy(d);
+        return fail(BCH_ENOMEM, "row-parallel tables");
+    }
+    if (he != hipSuccess) {
+        bch_decoder_destroy(d);
+        return hip_fail(he, "row-parallel tables");
     }
     if (hipDeviceGetAttribute(&d->n_cu, hipDeviceAttributeMultiprocessorCount, d->dev) != hipSuccess ||
         d->n_cu <= 0)
@@ -732,6 +767,8 @@ void bch_decoder_destroy(bch_decoder dec)
         (void)hipFree(dec->d_hcol);
     if (dec->d_rowpar)
         (void)hipFree(dec->d_rowpar);
+    if (dec->d_rowgen)
+        (void)hipFree(dec->d_rowgen);
     delete dec;
 }
 
@@ -806,7 +843,9 @@ int bch_nms_decode_batch(bch_decoder dec, const void *llr, int64_t ld, int64_t F
     float *ws = static_cast<float *>(workspace);
     a.ws_c2v = ws;
     a.ws_s = ws ? ws + (size_t)a.B * a.E * F : nullptr;
-    hipError_t e = launch_generic_fp32(a, stream);
+    // the frame-per-workgroup kernel wherever its tables and state fit (24-400
+    // times the other's rate, k_rowgen.hip), whatever the call's size
+    hipError_t e = dec->d_rowgen ? launch_rowgen(a, dec->rowgen, stream) : launch_generic_fp32(a, stream);
     return e == hipSuccess ? BCH_OK : hip_fail(e, "generic kernel launch");
 }
 

@@ -84,89 +84,178 @@ size_t rowpar_lds_bytes(int N, int M, int dp)
     return 4 * 3 * ext + 8 * 3 * (size_t)(3 * M + 2) + 4 * 2 * 3 * us;
 }
 
-bool build_rowpar(const Pcm &p, RowParImage &out)
+namespace {
+
+// Rounds of 64 rows (s, r), s < ns: steps, masks and record slots.  stride:
+// bytes of a record; where: if not null, receives each row's columns in the
+// order read, [s * M + r][position] (the pad cell for a lane that sits out).
+void build_rounds(const Pcm &p, int ns, int dp, int stride, RowParImage &out, std::vector<std::vector<int>> *where)
 {
-    const int N = p.N, M = p.M, dp = shift_period(N);
-    const int ext = N + 2 * dp;  // cells of a type's extended input; cell ext is the pad (+inf)
-    if (8 * (3 * M + 2) > 65535)
-        return false;
+    const int N = p.N, M = p.M;
+    const int ext = N + (ns - 1) * dp;  // cells of a type's extended input; cell ext is the pad (+inf)
     struct Item {
         int s, r, w;
     };
     std::vector<Item> items;
-    for (int s = 0; s < 3; s++)
+    for (int s = 0; s < ns; s++)
         for (int r = 0; r < M; r++)
             items.push_back({s, r, p.rows[r].weight()});
     // rows of like weight share a round, which then takes the steps of its heaviest row
     std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.w > b.w; });
     const int R = (int)(items.size() + kLanes - 1) / kLanes;
     std::vector<uint32_t> steps, rounds, mask, slot;
+    if (where)
+        where->assign(ns * M, {});
     for (int q = 0; q < R; q++) {
         std::vector<std::vector<int>> cells(kLanes);
         int w = 0;
         for (int l = 0; l < kLanes; l++) {
             const size_t t = (size_t)q * kLanes + l;
             uint32_t mk[4] = {0, 0, 0, 0};
-            int sl = 3 * M + 1;  // idle lanes write a record nobody reads
+            int sl = ns * M + 1;  // idle lanes write a record nobody reads
             if (t < items.size()) {
                 const Item &it = items[t];
                 sl = it.s * M + it.r;
                 for (int i = 0; i < N; i++)
                     if (p.rows[it.r].get(i)) {
-                        cells[l].push_back(i - it.s * dp + 2 * dp);
+                        cells[l].push_back(i + (ns - 1 - it.s) * dp);
                         const int k = ((i - it.s * dp) % N + N) % N;
                         mk[k >> 5] |= 1u << (k & 31);
                     }
                 w = std::max(w, it.w);
             }
             mask.insert(mask.end(), mk, mk + 4);
-            slot.push_back((uint32_t)(8 * sl));
+            slot.push_back((uint32_t)(stride * sl));
         }
-        const int ns = (w + kRpCols - 1) / kRpCols;
-        order_cells(cells, ns * kRpCols, ext);
-        for (int e = 0; e < ns; e++)
+        const int n = (w + kRpCols - 1) / kRpCols;
+        order_cells(cells, n * kRpCols, ext);
+        for (int e = 0; e < n; e++)
             for (int l = 0; l < kLanes; l++)
                 for (int h = 0; h < kRpCols / 2; h++) {
                     const uint32_t a = 4u * cells[l][e * kRpCols + 2 * h];
                     const uint32_t b = 4u * cells[l][e * kRpCols + 2 * h + 1];
                     steps.push_back(a | (b << 16));
                 }
-        rounds.push_back((uint32_t)ns);
+        rounds.push_back((uint32_t)n);
+        out.sign_words = std::max(out.sign_words, (n * kRpCols + kRgSigns - 1) / kRgSigns);
+        if (where)
+            for (int l = 0; l < kLanes && (size_t)q * kLanes + l < items.size(); l++) {
+                const Item &it = items[(size_t)q * kLanes + l];
+                (*where)[it.s * M + it.r] = cells[l];
+            }
     }
     // one more step: the kernel reads a step ahead
     steps.insert(steps.end(), 3 * kLanes, 0u);
-    // records of coordinate k in the order of the sums: shift 0's rows, 1's, 2's
-    const int nk = N > kLanes ? 2 : 1;
-    std::vector<std::vector<int>> lists(nk * kLanes);
-    size_t most = 0;
-    for (int k = 0; k < N; k++) {
-        for (int s = 0; s < 3; s++)
-            for (int r = 0; r < M; r++)
-                if (p.rows[r].get((k + s * dp) % N))
-                    lists[k].push_back(s * M + r);
-        most = std::max(most, lists[k].size());
-    }
-    const int C = (int)(most + kRpRecs - 1) / kRpRecs;
-    std::vector<uint32_t> recs;
-    for (int c = 0; c < C + 1; c++)
-        for (int k = 0; k < nk * kLanes; k++)
-            for (int h = 0; h < kRpRecs / 2; h++) {
-                uint32_t v[2];
-                for (int j = 0; j < 2; j++) {
-                    const size_t e = (size_t)c * kRpRecs + 2 * h + j;
-                    v[j] = 8u * (uint32_t)(e < lists[k].size() ? lists[k][e] : 3 * M);  // 3 M: the zero record
-                }
-                recs.push_back(v[0] | (v[1] << 16));
-            }
-    out.data.clear();
     out.steps = append(out.data, steps.data(), steps.size() * 4);
     out.rounds = append(out.data, rounds.data(), rounds.size() * 4);
     out.mask = append(out.data, mask.data(), mask.size() * 4);
     out.slot = append(out.data, slot.data(), slot.size() * 4);
-    out.recs = append(out.data, recs.data(), recs.size() * 4);
     out.n_rounds = R;
-    out.n_recs = (int)most;
+}
+
+// Chunks of four 16-bit record offsets, [chunk][coordinate], zero records past
+// a list's end; one chunk more than the longest list, which the kernel reads ahead.
+int append_lists(const std::vector<std::vector<int>> &lists, int stride, int zero, std::vector<uint32_t> &recs)
+{
+    size_t most = 0;
+    for (const auto &l : lists)
+        most = std::max(most, l.size());
+    const int C = (int)(most + kRpRecs - 1) / kRpRecs;
+    for (int c = 0; c < C + 1; c++)
+        for (const auto &l : lists)
+            for (int h = 0; h < kRpRecs / 2; h++) {
+                uint32_t v[2];
+                for (int j = 0; j < 2; j++) {
+                    const size_t e = (size_t)c * kRpRecs + 2 * h + j;
+                    v[j] = (uint32_t)(stride * (e < l.size() ? l[e] : zero));
+                }
+                recs.push_back(v[0] | (v[1] << 16));
+            }
+    return (int)most;
+}
+
+}  // namespace
+
+bool build_rowpar(const Pcm &p, RowParImage &out)
+{
+    const int N = p.N, M = p.M, dp = shift_period(N);
+    constexpr int kRec = 8;
+    if (kRec * (3 * M + 2) > 65535)
+        return false;
+    out = RowParImage();
+    build_rounds(p, 3, dp, kRec, out, nullptr);
+    // records of coordinate k in the order of the sums: shift 0's rows, 1's, 2's
+    std::vector<std::vector<int>> lists(N > kLanes ? 2 * kLanes : kLanes);
+    for (int k = 0; k < N; k++)
+        for (int s = 0; s < 3; s++)
+            for (int r = 0; r < M; r++)
+                if (p.rows[r].get((k + s * dp) % N))
+                    lists[k].push_back(s * M + r);
+    std::vector<uint32_t> recs;
+    out.n_recs = append_lists(lists, kRec, 3 * M, recs);
+    out.recs = append(out.data, recs.data(), recs.size() * 4);
     return true;
+}
+
+int rowgen_stride(const RowParImage &im, bool memory)
+{
+    return memory ? 4 * ((3 + im.sign_words + 1) & ~1) : 8;
+}
+
+bool build_rowgen(const Pcm &p, int n_branches, bool memory, RowParImage &out)
+{
+    const int N = p.N, M = p.M, ns = n_branches > 1 ? 3 : 1, dp = n_branches > 1 ? shift_period(N) : 0;
+    out = RowParImage();
+    // the stride of a row's state depends on its steps, known from the heaviest row
+    int w = 0;
+    for (const Row &r : p.rows)
+        w = std::max(w, r.weight());
+    out.sign_words = ((w + kRpCols - 1) / kRpCols * kRpCols + kRgSigns - 1) / kRgSigns;
+    const int stride = rowgen_stride(out, memory);
+    if ((long)stride * (ns * M + 2) > 65535)
+        return false;
+    std::vector<std::vector<int>> where;
+    build_rounds(p, ns, dp, stride, out, &where);
+    const int n = N > kLanes ? 2 * kLanes : kLanes;
+    std::vector<uint32_t> recs;
+    for (int s = 0; s < ns; s++) {
+        std::vector<std::vector<int>> lists(n), pos(n);
+        size_t most = 0;
+        for (int k = 0; k < N; k++) {
+            const int i = (k + s * dp) % N;
+            for (int r = 0; r < M; r++)
+                if (p.rows[r].get(i)) {
+                    const std::vector<int> &c = where[s * M + r];
+                    const int e = (int)(std::find(c.begin(), c.end(), i + (ns - 1 - s) * dp) - c.begin());
+                    // sign of position e: bit `last - e` of its word, whose positions end at `last`
+                    const int word = e / kRgSigns, last = std::min(kRgSigns * (word + 1), (int)c.size()) - 1;
+                    lists[k].push_back(s * M + r);
+                    pos[k].push_back(e | (32 * word + last - e) << 8);
+                }
+            most = std::max(most, lists[k].size());
+        }
+        out.seg[s] = (int)most;
+        if (!memory) {
+            append_lists(lists, stride, ns * M, recs);
+            continue;
+        }
+        for (size_t e = 0; e < most + 1; e++)
+            for (int k = 0; k < n; k++) {
+                const bool in = e < lists[k].size();
+                recs.push_back((uint32_t)(stride * (in ? lists[k][e] : ns * M)) | (uint32_t)(in ? pos[k][e] : 0) << 16);
+            }
+    }
+    out.recs = append(out.data, recs.data(), recs.size() * 4);
+    return true;
+}
+
+size_t rowgen_lds_bytes(const RowGenTab &t, int N, int M, int mode)
+{
+    const size_t ext = (size_t)((N + (t.ns - 1) * t.dp + 4) & ~3);
+    size_t n = 32 + 4 * t.np * ext + (size_t)t.stride * t.np * (t.ns * M + 2);
+    if (mode == BCH_MODE_MEMORY)
+        n += 4 * (size_t)t.np * t.ns * ext;
+    return n;
 }
 
 }  // namespace bch

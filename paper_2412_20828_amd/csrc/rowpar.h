@@ -52,6 +52,8 @@ struct RowParImage {
     std::vector<uint8_t> data;
     size_t steps = 0, rounds = 0, mask = 0, slot = 0, recs = 0;
     int n_rounds = 0, n_recs = 0;
+    int seg[3] = {0, 0, 0};  // generic kernels: records of a coordinate in shift s (the longest list)
+    int sign_words = 0;      // words of a row's message signs
 };
 
 // Tables of the nine-branch restart-mode decode of matrix p; false if an
@@ -60,6 +62,35 @@ bool build_rowpar(const Pcm &p, RowParImage &out);
 
 // LDS bytes of one workgroup on this code
 size_t rowpar_lds_bytes(int N, int M, int dp);
+
+// ---- generic decoder (k_rowgen.hip): any matrix, 1, 3 or 9 branches, all
+// message modes.  The sums run over the shifts, then the types, so a
+// coordinate's records are listed shift by shift.  With edge memory
+// (memory = true) a list entry is a 32-bit word: byte offset of the row's
+// state | the entry's position in the row << 16 | (32 word + bit) << 24 of the
+// position's sign.
+constexpr int kRgSigns = 30;  // positions (five table steps) whose signs share a word
+
+struct RowGenTab {
+    const uint32_t *steps;
+    const uint32_t *rounds;
+    const uint4 *mask;
+    const uint32_t *slot;
+    const uint32_t *recs;    // restart: uint2 chunks of four 16-bit offsets; else 32-bit entries
+    int n_rounds;
+    int seg[3];
+    int stride;              // bytes of a row's record or state
+    int ns, np;              // shifts and types
+    int dp;                  // shift period, 0 for one branch
+    int offsets;             // d_o is used (more than one branch)
+};
+
+bool build_rowgen(const Pcm &p, int n_branches, bool memory, RowParImage &out);
+int rowgen_stride(const RowParImage &im, bool memory);
+size_t rowgen_lds_bytes(const RowGenTab &t, int N, int M, int mode);
+
+struct GenericArgs;
+hipError_t launch_rowgen(const GenericArgs &a, const RowGenTab &t, hipStream_t stream);
 
 hipError_t launch_rowpar(const RowParArgs &a, int fix8, hipStream_t stream);
 
