@@ -158,15 +158,18 @@ enum {
                                   lane, same results), registered for the four workload
                                   matrices of N = 63 and 127.  Without this flag a fixed-point
                                   decode of at least 4,000,000 frames (N = 127) or 8,000,000
-                                  (N = 63) runs it where registered, a smaller one the kernel
-                                  that holds its integers in 32-bit registers */
+                                  (N = 63) runs it where registered and where the kernel with
+                                  its sums on the matrix cores (bch_decoder_kernel_name) does
+                                  not stand in for it, a smaller one the kernel that holds its
+                                  integers in 32-bit registers */
     BCH_DEC_SMALL_ALWAYS = 4,  /* N = 127: always use the small-batch kernel (the nine
                                   branches of 64 frames on three waves) where registered */
     BCH_DEC_SMALL_NEVER = 8,   /* N = 127: never use it.  Without either flag a decode of at
                                   most 128 frames per CU runs the row-parallel kernel, a
                                   larger one the kernel of one wave per 64 frames; either
-                                  flag also excludes the row-parallel kernel (both code
-                                  lengths); the results are the same.
+                                  flag also excludes the row-parallel kernel and the one with
+                                  its sums on the matrix cores (both code lengths); the
+                                  results are the same.
                                   Both flags together, or any other bit, give BCH_EINVAL */
     BCH_DEC_UNPACKED16 = 16,   /* BCH_FIX8: never the packed 16-bit kernel (with
                                   BCH_DEC_PACKED16: BCH_EINVAL) */
@@ -207,7 +210,10 @@ int bch_decoder_is_specialized(bch_decoder dec);
  * 128 frames per CU, N = 63: 224, a mixed-code call without either of its
  * flags: 256) on the row-parallel kernel instead, a frame per workgroup in one
  * launch, with the same results bit for bit; the name is that of the
- * lane-per-frame kernel it stands in for. */
+ * lane-per-frame kernel it stands in for.  So it is with the fixed-point kernel
+ * whose sums run on the matrix cores, in decoders without those three flags:
+ * (127,64) with 72 and (127,99) with 33 rows from 96 frames per CU on (the
+ * row-parallel kernel's limit there), (63,36) with 122 rows from 2400. */
 const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F);
 void bch_decoder_destroy(bch_decoder dec);
 
@@ -251,7 +257,9 @@ int bch_nms_decode_batch_noalloc(bch_decoder dec, const void *llr, int64_t ld, i
  * persistent grid (0: the kernel's default; the nine-branch N = 63 kernels
  * run workgroups of three waves, so waves_per_cu / 3 of them per CU).  A
  * decode of F frames never launches more than its frames can occupy.  No
- * effect on the generic and the row-parallel kernel.  Not thread-safe against a concurrent
+ * effect on the generic and the row-parallel kernel; the kernel with its
+ * sums on the matrix cores runs no more than its own waves (four per CU, eight
+ * for N = 63).  Not thread-safe against a concurrent
  * decode. */
 int bch_decoder_set_tuning(bch_decoder dec, int waves_per_cu);
 
@@ -272,7 +280,7 @@ int bch_decoder_set_tuning(bch_decoder dec, int waves_per_cu);
  * over: one launch saves the per-code launch tails, which dominate small
  * batches, while at large batches each code's own kernel is faster (the
  * 63-bit codes' kernels run three waves per SIMD, the mixed kernel one, and
- * large fixed-point calls take the packed 16-bit kernels).  Calls of at most
+ * large fixed-point calls take kernels of their own).  Calls of at most
  * 256 frames per CU run the row-parallel kernel (bch_decoder_kernel_name) in
  * one launch of any codes, unless a decoder has one of those two flags or
  * excludes it.  No host synchronisation, no memset: the call

@@ -36,6 +36,7 @@ struct bch_decoder_s {
     const bch::SpecKernel *spec = nullptr;        // throughput kernel
     const bch::SpecKernel *spec_small = nullptr;  // small-batch kernel (N = 127), or null
     const bch::SpecKernel *spec_packed = nullptr; // fixed point: packed 16-bit kernel for large calls, or null
+    const bch::SpecKernel *spec_mm = nullptr;     // fixed point: kernel with its sums on the matrix cores, or null
     uint64_t fingerprint = 0;                     // of the matrix (mixed-code kernel lookup)
     uint8_t *d_rowpar = nullptr;                  // tables of the row-parallel kernel, or null: never use it
     bch::RowParTab rowpar{};
@@ -130,6 +131,25 @@ static const bch::SpecKernel *spec_for(const bch_decoder_s *d, int64_t F)
     return d->spec;
 }
 
+// fixed point: smallest call of the kernel with its sums on the matrix cores
+// (nms_spec_mm.inc) where it is registered.  Measured in us per call against
+// the kernel it stands in for, on 256 CUs, at 2 / 3 / 5 dB:
+//   N = 127, 72 rows   40000: 737 / 725 / 716, 1369 / 1362 / 1355
+//                      262144: 3014 / 2664 / 1338, 5992 / 5225 / 2602
+//   N = 127, 33 rows   1500000 at 3 dB: 11150, 26767
+//   N = 63, 122 rows   600000: 3131 / 2258 / 1738, 4589 / 3041 / 1749
+//                      200000: 1596 / 1513 / 1185, 1794 / 1391 / 1019
+// hence every call of N = 127, and 2400 frames per CU for N <= 64, where eight
+// of its waves fill a CU against twelve, each with a longer iteration, so that
+// the end of a call weighs more.
+static int64_t mm_min_frames(const bch_decoder_s *d) { return d->N > 64 ? 0 : (int64_t)d->n_cu * 2400; }
+
+// the lane-per-frame kernel that a decode of F frames runs
+static const bch::SpecKernel *spec_run(const bch_decoder_s *d, int64_t F)
+{
+    return d->spec_mm && F >= mm_min_frames(d) ? d->spec_mm : spec_for(d, F);
+}
+
 // device workspace of one specialised decode of up to F frames
 static int spec_offsets(const bch_decoder_s *d) { return d->prm.n_branches > 1 ? shift_period(d->N) : 1; }
 
@@ -182,9 +202,10 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
     // no more persistent waves than a batch of F frames can keep busy (small
     // batches launch small grids): ceil(F / frames per workgroup) + dp
     // workgroups of wave_group waves.  The tuned waves per CU belong to the
-    // throughput kernel.
-    const bch::SpecKernel *k = spec_for(d, F);
-    const int waves = k == d->spec ? waves_of(d) : k->waves_per_cu;
+    // throughput kernel; the one in its place runs no more than its own.
+    const bch::SpecKernel *k = spec_run(d, F);
+    const int waves = k == d->spec ? waves_of(d)
+                      : k == d->spec_mm ? std::min(waves_of(d), k->waves_per_cu) : k->waves_per_cu;
     const int64_t grid = (int64_t)d->n_cu * waves;
     const int g = k->wave_group;
     const int64_t fw = k->frames_per_wave;
@@ -208,11 +229,18 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
 //   N = 63, 122 rows  32768: 650 / 939, 349 / 924   49152: 866 / 1074, 486 / 1069
 //                     65536: 1110 / 1115, 629 / 1105 (fixed point 1202 / 1169)
 //   N = 63, 33 rows   32768: 192 / 306, 122 / 300   65536: 348 / 370, 222 / 366
-// hence 128 frames per CU for N > 64 and 224 for N <= 64.  A mixed-code call of
+// hence 128 frames per CU for N > 64 and 224 for N <= 64.  Against the kernel
+// with its sums on the matrix cores (fixed point, N = 127, 72 rows; about 730
+// at each of these sizes and Eb/N0) it takes, at 2 / 3 / 5 dB,
+//   16384: 704 / 575 / 191   24576: 968 / 794 / 255   32768: 1233 / 1029 / 334
+// hence 96 frames per CU there.  A mixed-code call of
 // the service's four codes takes 899 / 1450 us at 32768 frames, 1684 / 1731 at
 // 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455 at 65536 over 2-5 dB):
 // 256 per CU.
-static int64_t rowpar_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * (d->N > 64 ? 128 : 224); }
+static int64_t rowpar_max_frames(const bch_decoder_s *d)
+{
+    return (int64_t)d->n_cu * (d->N <= 64 ? 224 : d->spec_mm ? 96 : 128);
+}
 static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
 
 // one launch of the row-parallel kernel: frame f with decs[code_idx[f]] (or
@@ -721,6 +749,9 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
             d->spec_small = find_spec_kernel(p, q, 2);
         if (d->spec && !packed && q.precision == BCH_FIX8 && !(q.flags & BCH_DEC_UNPACKED16))
             d->spec_packed = find_spec_kernel(p, q, 1);
+        if (d->spec && q.precision == BCH_FIX8 &&
+            !(q.flags & (BCH_DEC_PACKED16 | BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER)))
+            d->spec_mm = find_spec_kernel(p, q, 3);
     }
     d->fingerprint = pcm_fingerprint(p);
     try {

@@ -17,7 +17,8 @@ import numpy as np
 # (code name, target rows of H_o (0: the standard matrix), n_branches, mode
 #  (1 restart, 3 extrinsic messages), precision (0 FP32, 1 FIX8), waves per CU
 #  of the persistent grid[, variant: 1 = packed 16-bit fixed point, 2 = three
-#  waves per 64 frames for N = 127, the kernel for small batches])
+#  waves per 64 frames for N = 127, the kernel for small batches, 3 = fixed point
+#  with the c2v sums on the matrix cores])
 SPECS = [
     ("bch63_45", 33, 9, 1, 0, 12),
     ("bch63_36", 122, 9, 1, 0, 12),
@@ -34,6 +35,10 @@ SPECS = [
     ("bch63_36", 122, 9, 1, 1, 8, 1),
     ("bch127_99", 33, 9, 1, 1, 4, 1),
     ("bch127_64", 72, 9, 1, 1, 4, 1),
+    # fixed point with the c2v sums on the matrix cores
+    ("bch63_36", 122, 9, 1, 1, 8, 3),
+    ("bch127_99", 33, 9, 1, 1, 4, 3),
+    ("bch127_64", 72, 9, 1, 1, 4, 3),
     # small batches of the 127-bit codes: the branch types of 64 frames on
     # three waves (one workgroup per CU)
     ("bch127_99", 33, 9, 1, 0, 3, 2),
@@ -579,6 +584,93 @@ def body_source_pk16(H: np.ndarray, B: int) -> str:
     return "\n".join(out)
 
 
+def body_source_mm(H: np.ndarray, dp: int, split: bool, B: int = 9) -> str:
+    """Tables and row functions of the fixed-point decoder with its sums on the
+    matrix cores (nms_spec_mm.inc).  Rows of a type: rho = s M + r, matrix row r
+    at cyclic shift s, on the shift-0 input (see shift_matrices); they go
+    through the sum product in one stage, or (split) a stage per shift.  A
+    stage's Rows<stage>::run searches each row's two least keys, forms s q1 (a
+    byte of X, four rows a word, 16 rows a 16-byte store) and adds s (q2 - q1)
+    to the argmin's correction word.  W holds the rows' sign parities, row rho
+    at bit 4 (T mod 8) + r of word 4 (T / 8) + g, rho = 16 T + 4 g + r (the layout
+    of a 16 x 16 product)."""
+    M, N = H.shape
+    if int(H.sum(axis=0).max()) * 96 * B > 32767:
+        raise ValueError("a coordinate's corrections could pass 16 bits")
+    rows = [np.nonzero(r)[0].tolist() for Hs in shift_matrices(H, dp) for r in Hs]
+    size = M if split else 3 * M
+    stages = [list(range(k, k + size)) for k in range(0, 3 * M, size)]
+    TP, G16, KP, KS = (3 * M + 15) // 16, (N + 15) // 16, (N + 63) // 64, (size + 63) // 64
+    par = np.zeros((16 * TP, 64 * KP), np.uint8)
+    main = np.zeros((len(stages), 16 * G16, 64 * KS), np.uint8)
+    for rho, cols in enumerate(rows):
+        par[rho, cols] = 1
+        main[rho // size, cols, rho % size] = 1
+    out = []
+    for name, t in (("PAR", par), ("MAIN", main)):
+        out.append("__device__ const __attribute__((aligned(16))) uint8_t %s%s = {"
+                   % (name, "".join("[%d]" % n for n in t.shape)))
+        out += ["    %s," % np.array2string(x, separator=",", threshold=1 << 30, max_line_width=1 << 30)
+                .replace("[", "{").replace("]", "}").replace(" ", "") for x in t]
+        out.append("};")
+    out += ["__device__ __forceinline__ void add_word(uint8_t *p, uint32_t v)", "{",
+            "    __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(p), v, __ATOMIC_RELAXED, "
+            "__HIP_MEMORY_SCOPE_WAVEFRONT);", "}",
+            "__device__ __forceinline__ uint32_t bytes4(int a, int b, int c, int d)", "{",
+            "    const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);",
+            "    const uint32_t hi = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);",
+            "    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);", "}",
+            "template <int STAGE> struct Rows;"]
+
+    def search(rho):
+        # the row's keys opaque: else the compiler shares partial minima between
+        # rows (cyclic shifts of few) and spills them
+        st = ['__asm__("" : "+v"(K[%d]));' % c for c in rows[rho]]
+        return st + [x for step in _min_steps(rows[rho], "_%d" % rho, lambda c: "K[%d]" % c) for x in step]
+
+    def finish(rho):
+        T, q, r = rho // 16, rho // 4 % 4, rho % 4
+        f = dict(s="_%d" % rho, w=4 * (T // 8) + q, b=31 - (4 * (T % 8) + r))
+        # the parity bit as 0 / -1, then s = +1 / -1
+        return [x % f for x in (
+            "const int s%(s)s = ((int)(W[%(w)d] << %(b)d) >> 31) | 1;",
+            "const int q1%(s)s = (int)(u1%(s)s >> 15), x%(s)s = __mul24(q1%(s)s, s%(s)s);",
+            "const int d%(s)s = __mul24((int)(u2%(s)s >> 15) - q1%(s)s, s%(s)s);",
+            "add_word(co + ((u1%(s)s & 0x3f00u) | lane4), (uint32_t)d%(s)s << (u1%(s)s & 31u));")]
+
+    for st, rhos in enumerate(stages):
+        out += ["template <> struct Rows<%d> {" % st,
+                "__device__ static __forceinline__ void run(uint32_t *__restrict__ K, const uint32_t *__restrict__ W, "
+                "uint8_t *X, uint8_t *co, uint32_t lane4)", "{"]
+        # a row's search shares a scheduling region with the last steps of the
+        # row before, whose chain of dependent instructions it fills
+        out += ["    " + x for x in search(rhos[0])]
+        for k, rho in enumerate(rhos):
+            if k + 1 < len(rhos):
+                out += ["    " + x for x in search(rhos[k + 1])]
+            out += ["    " + x for x in finish(rho)]
+            if k % 16 == 15 or k + 1 == len(rhos):
+                T = k // 16
+                names = ["x_%d" % rhos[i] if i < len(rhos) else "0" for i in range(16 * T, 16 * T + 16)]
+                words = ", ".join("bytes4(%s)" % ", ".join(names[4 * q:4 * q + 4]) for q in range(4))
+                out.append("    *reinterpret_cast<uint4 *>(X + %d) = make_uint4(%s);" % (1024 * T, words))
+            out.append("    __builtin_amdgcn_sched_barrier(0);")
+        out += ["}", "};"]
+    return "\n".join(out)
+
+
+def syndrome_source_mm(Hs: np.ndarray) -> str:
+    """eq. 5 on decisions in the layout of the matrix products: coordinate
+    16 t + 4 g + r at bit 4 t + r of S[g]."""
+    out = ["__device__ __forceinline__ bool syndrome_zero(const uint32_t *S)", "{", "    uint32_t odd = 0;"]
+    for row in Hs:
+        masks = [0, 0, 0, 0]
+        for u in np.nonzero(row)[0].tolist():
+            masks[(u >> 2) & 3] |= 1 << (4 * (u >> 4) + (u & 3))
+        out.append("    odd |= %s;" % _parity("S", masks))
+    return "\n".join(out + ["    return (odd & 1u) == 0;", "}"])
+
+
 def shift_matrices(H: np.ndarray, dp: int, ns: int = 3):
     """The matrix of each cyclic shift s d_p (s < ns) in the frame of shift 0:
     the row function of branch s reads entry c of the shifted input at index
@@ -636,13 +728,16 @@ def generate(stage1_lib: str, out_dir: str):
         H, Hs = mats[(name, rows)]
         M, N = H.shape
         ns = "spec_%s_m%d_b%d%s%s%s" % (name, M, B, "_fix8" if prec else "",
-                                         {0: "", 1: "_pk16", 2: "_grp"}[variant], "_ext" if mode == 3 else "")
+                                         {0: "", 1: "_pk16", 2: "_grp", 3: "_mm"}[variant], "_ext" if mode == 3 else "")
         body_path = os.path.join(out_dir, ns + "_body.inc")
         regacc = 1 if B > 1 else 0
         pk16 = 1 if prec and regacc and variant == 1 else 0
         # nine branches: three waves (one per automorphism type) share each 64
         # frames; always for N = 63, as the small-batch kernel for N = 127
         group = 1 if regacc and B == 9 and ((N <= 64 and variant == 0) or variant == 2) else 0
+        mm = variant == 3
+        if mm and not (prec and B == 9 and mode == 1):
+            raise ValueError("the matrix-core variant is for nine branches in fixed point")
         if variant == 1 and not pk16:
             raise ValueError("the packed variant needs fixed point and 3 or 9 branches")
         if variant == 2 and not (group and N > 64):
@@ -660,6 +755,8 @@ def generate(stage1_lib: str, out_dir: str):
             fh.write("// generated: %s, H %d x %d, %d edges\n" % (name, M, N, int(H.sum())))
             if ext:
                 fh.write(body_source_ext(H))
+            elif mm:
+                fh.write(body_source_mm(H, dp, N <= 64))
             elif pk16 and fold:
                 fh.write(folded_body_source(H, dp, lambda Hs: body_source_pk16(Hs, B)))
             elif pk16:
@@ -676,7 +773,7 @@ def generate(stage1_lib: str, out_dir: str):
                     fh.write(body_source_ilp(H, fix8=bool(prec), group=ILP_ROWS, tree=True))
                 else:
                     fh.write(body_source_fix8(H, regacc) if prec else body_source(H, regacc))
-            fh.write("\n\n" + syndrome_source(Hs) + "\n")
+            fh.write("\n\n" + (syndrome_source_mm(Hs) if mm else syndrome_source(Hs)) + "\n")
         src_path = os.path.join(out_dir, ns + ".hip")
         with open(src_path, "w") as fh:
             fh.write('#include "spec_launch.h"\n')
@@ -687,14 +784,16 @@ def generate(stage1_lib: str, out_dir: str):
             fh.write('#define SPEC_BODY "%s"\n' % os.path.basename(body_path))
             if group and N > 64:
                 fh.write("#define SPEC_WAVES_PER_SIMD 1\n")
-            if ext:
+            if ext or mm:
                 fh.write("#define SPEC_M %d\n" % M)
+            if mm:
+                fh.write("#define SPEC_SPLIT %d\n" % (N <= 64))
             if fold:
                 fh.write("#define SPEC_FOLD 1\n")
             if not (pk16 or group):
                 fh.write("#define SPEC_RESERVE %d\n" % (RESERVE if ext or B < 9 else 0))
-            fh.write('#include "%s"\n' % ("nms_spec_ext.inc" if ext else "nms_spec_pk16.inc" if pk16 else
-                                           "nms_spec_group.inc" if group else "nms_spec_fp32.inc"))
+            fh.write('#include "%s"\n' % ("nms_spec_ext.inc" if ext else "nms_spec_mm.inc" if mm else
+                                           "nms_spec_pk16.inc" if pk16 else "nms_spec_group.inc" if group else "nms_spec_fp32.inc"))
         srcs.append(src_path)
         decls.append("namespace %s { hipError_t launch(const SpecLaunch &, int, int, hipStream_t); }" % ns)
         entries.append("    {0x%016xull, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, \"%s\", &%s::launch}," %
