@@ -82,15 +82,15 @@ FIX_SCALE = 4.0
 # and of the generator functions that write its row function); any other build
 # reports traffic null.
 TRAFFIC_B_PER_FRAME = {  # kernel: (fetched, written, family, source hash)
-    "spec_bch127_64_m72_b9": (523.11, 90.35, "one_wave", "0a4d801252c7f5af"),
-    "spec_bch127_99_m33_b9": (522.03, 88.35, "one_wave", "0a4d801252c7f5af"),
+    "spec_bch127_64_m72_b9": (522.89, 92.67, "one_wave", "e784f371a504277c"),
+    "spec_bch127_99_m33_b9": (522.57, 89.23, "one_wave", "e784f371a504277c"),
     "spec_bch127_64_m72_b9_fix8_pk16": (135.90, 84.46, "pk16", "80d070ec35864e98"),
     "spec_bch127_99_m33_b9_fix8_pk16": (135.65, 85.67, "pk16", "80d070ec35864e98"),
 }
 KERNEL_FAMILIES = {
     "one_wave": (["csrc/nms_spec_fp32.inc", "csrc/nms_spec_rot.inc", "csrc/nms_spec_cursor.inc"],
                  ["body_source_ilp", "_min_steps", "syndrome_source", "_sign_masks", "_parity", "_MED3U",
-                  "ILP_ROWS", "FOLD_SHIFTS", "FOLD_EXCLUDE", "folded_body_source", "shift_matrices"]),
+                  "ILP_ROWS", "FOLD_SHIFTS", "LDS_COLUMNS", "Dual", "folded_body_source", "shift_matrices"]),
     "pk16": (["csrc/nms_spec_pk16.inc", "csrc/nms_spec_rot.inc", "csrc/nms_spec_cursor.inc"],
              ["body_source_pk16", "syndrome_source", "_parity", "PK16_GROUP", "FOLD_SHIFTS",
               "folded_body_source", "shift_matrices"]),

@@ -83,10 +83,12 @@ ILP_ROWS = 1
 # type then gathers its input once instead of three times, and its sums need
 # no register rotation between the shifts
 FOLD_SHIFTS = True
-# one-wave kernels left unfolded: folded, BCH(127,99)'s 33-row kernels spill
-# 33 registers to scratch instead of 3 (measured: 194 B of HBM writes per
-# frame instead of 88, for 2.2% less time)
-FOLD_EXCLUDE = {("bch127_99", 33)}
+# one-wave N = 127 kernels: columns whose entries the row function reads from
+# LDS instead of registers, of the 31 that fit a CU's 160 KiB beside four
+# waves' y: with fewer, registers spill into moves, with more, the reads cost
+# more than they save (2,000,000 frames of (127,64) / (127,99) at 2 dB, ms: 16
+# columns 34.1 / 28.9, 20 34.0 / 28.6, 24 34.3 / 28.9, 31 34.3 / 29.0)
+LDS_COLUMNS = 20
 # entries whose update steps the packed 16-bit row function interleaves
 PK16_GROUP = 4
 # edges between scheduling barriers in the extrinsic-message row function
@@ -203,6 +205,73 @@ def _parity(S, masks):
     return "__builtin_popcount(%s)" % " ^ ".join(terms)
 
 
+class Dual:
+    """Sign parities of check rows from the syndrome bits of one dual codeword.
+
+    Every row of H, at any cyclic shift, is a sum of the shifts i < n_dual of a
+    row w of H whose first n_dual shifts are independent (the dual code is
+    cyclic and of dimension n_dual = N - K).  So a row's sign parity is the
+    parity of some bits of Z, the bits z_i = parity of the signs on w shifted
+    by i, which are the XOR of one window of the sign string per entry of w:
+    ceil(n_dual / 32) words a row to mask and fold instead of ceil(N / 32).
+    Z[i / 32] holds z_i at bit 31 - i mod 32."""
+
+    def __init__(self, H: np.ndarray, n_dual: int):
+        self.N, self.n = H.shape[1], n_dual
+        for row in sorted(H.tolist(), key=sum):
+            taps = [c for c in range(self.N) if row[c]]
+            shifts = [sum(1 << (c + i) % self.N for c in taps) for i in range(n_dual)]
+            self.basis = {}  # leading bit: (vector, its combination of shifts)
+            for i, v in enumerate(shifts):
+                v, comb = self._reduce(v, 1 << i)
+                if v == 0:
+                    break
+                self.basis[v.bit_length()] = (v, comb)
+            if len(self.basis) == n_dual:
+                self.taps = taps
+                return
+        raise ValueError("no row of H spans the dual code by its shifts")
+
+    def _reduce(self, v, comb):
+        while v and v.bit_length() in self.basis:
+            b = self.basis[v.bit_length()]
+            v, comb = v ^ b[0], comb ^ b[1]
+        return v, comb
+
+    def masks(self, cols):
+        """Masks over Z of a row with these columns."""
+        v, comb = self._reduce(sum(1 << c for c in cols), 0)
+        if v:
+            raise ValueError("a row outside the dual code")
+        out = [0] * ((self.n + 31) // 32)
+        for i in range(self.n):
+            if comb >> i & 1:
+                out[i // 32] |= 1 << (31 - i % 32)
+        return out
+
+    def source(self):
+        """dual_bits(S, Z) on the sign words S of _sign_masks."""
+        N, W = self.N, (self.n + 31) // 32
+        out = ["__device__ __forceinline__ void dual_bits(const uint32_t *S, uint32_t *Z)", "{"]
+        last = (N - 1) // 32  # word of S that holds N mod 32 = 31 bits
+        for k in range(last + W + 1):  # E[k]: coordinates 32 k ... 32 k + 31 (mod N)
+            if k < last:
+                e = "S[%d]" % k
+            elif k == last:
+                e = "S[%d] << 1 | S[0] >> 31" % k
+            else:
+                j = k - last - 1
+                e = "S[%d] << 1 | S[%d] >> %d" % (j, j + 1, 30 if j + 1 == last else 31)
+            out.append("    const uint32_t e%d = %s;" % (k, e))
+        for j in range(W):
+            win = []
+            for t in self.taps:
+                k, r = (t + 32 * j) // 32, t % 32
+                win.append("__builtin_amdgcn_alignbit(e%d, e%d, %d)" % (k, k + 1, 32 - r) if r else "e%d" % k)
+            out.append("    Z[%d] = %s;" % (j, " ^ ".join(win)))
+        return "\n".join(out + ["}"])
+
+
 def _min_steps(cols, sfx, val, tree=True, pair_merge=True):
     """Steps (lists of statements) that leave u1<sfx> <= u2<sfx>, the two
     least of the row's values val(c), c in cols (integer form of non-negative
@@ -281,7 +350,7 @@ def _forward(cols):
 
 
 def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: bool = True,
-                    helpers: bool = True) -> str:
+                    helpers: bool = True, lds: int = 0, dual=None) -> str:
     """The row function (accumulating form, FP32 or fixed point) with
     independent work side by side, for kernels that run one wave per SIMD and
     so have no other wave to issue while an instruction waits for its
@@ -290,25 +359,56 @@ def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: boo
     independent triples per step already give the search its parallel work;
     else entry by entry), and the c2v selections of each row two edges at a
     time, pinned by scheduling barriers.  Every column is still updated by its
-    rows in ascending order."""
+    rows in ascending order.
+
+    lds > 0 (group 1): the entries of the first lds columns are read from LDS
+    columns AL[c][lane], each row's while the row before selects its messages,
+    through a pointer made opaque per row (else equal loads of all rows merge,
+    and the values fill the registers they were to free).
+
+    dual: S holds the bits of Dual instead of the sign words."""
     M, N = H.shape
-    out = ([_MED3U] if helpers else []) + ["__device__ __forceinline__ void body(const float *__restrict__ A, "
-                                           "const uint32_t *__restrict__ S, float *__restrict__ T)", "{"]
+    if lds and group != 1:
+        raise ValueError("columns in LDS: one row at a time")
+    out = ([_MED3U] if helpers else []) + ["__device__ __forceinline__ void body(%sfloat *__restrict__ A, %s"
+                                           "const uint32_t *__restrict__ S, float *__restrict__ T)"
+                                           % (("", "LdsColumns AL, ") if lds else ("const ", "")), "{"]
+
+    def fetch(j):
+        low = [int(c) for c in np.nonzero(H[j])[0] if c < lds]
+        if not low:
+            return []
+        return ['    __asm__ volatile("" : "+v"(AL));'] + [
+            "    const float a%d_%d = AL[%d];" % (j, c, 64 * c) for c in low]
+
+    def entry(j, c):
+        return "a%d_%d" % (j, c) if c < lds else "A[%d]" % c
+
+    out += fetch(0)
     for j0 in range(0, M, group):
         rows = list(range(j0, min(M, j0 + group)))
-        out.append("    { // rows %s" % ", ".join(map(str, rows)))
+        if lds:
+            out.append("    // row %d" % j0)
+        else:
+            out.append("    { // rows %s" % ", ".join(map(str, rows)))
         cols = {}
         for r, j in enumerate(rows):
+            r = j if lds else r
             cs = [int(c) for c in np.nonzero(H[j])[0]]
             cols[r] = cs
-            cnt = _parity("S", _sign_masks(cs, N))
+            cnt = _parity("S", dual.masks(cs) if dual else _sign_masks(cs, N))
             out.append("        const float sg%d = __uint_as_float(0x3f800000u | ((%s) << 31));" % (r, cnt))
-        steps = {r: _min_steps(cols[r], "_%d" % r, lambda c: "__float_as_uint(A[%d])" % c, tree=tree) for r in cols}
+        steps = {r: _min_steps(cols[r], "_%d" % r, lambda c, r=r: "__float_as_uint(%s)" % entry(r, c), tree=tree)
+                 for r in cols}
+        if lds:
+            out += ['        __asm__("" : "+v"(A[%d]));' % c for r in cols for c in cols[r] if c >= lds]
         for k in range(max(len(st) for st in steps.values())):
             for r in cols:
                 if k < len(steps[r]):
                     out += ["        " + x for x in steps[r][k]]
             out.append("        __builtin_amdgcn_sched_barrier(0);")
+        if lds and j0 + 1 < M:
+            out += fetch(j0 + 1)
         for r in cols:
             out.append("        const float m1_%d = __uint_as_float(u1_%d), m2_%d = __uint_as_float(u2_%d);"
                        % (r, r, r, r))
@@ -324,15 +424,16 @@ def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: boo
                 pair = cs[k:k + 2]
                 for q, c in enumerate(pair):
                     if fix8:
-                        sel = "__builtin_amdgcn_fmed3f(q1_%d, q2_%d, __builtin_fmaf(A[%d], -128.0f, K_%d))" % (
-                            r, r, c, r)
+                        sel = "__builtin_amdgcn_fmed3f(q1_%d, q2_%d, __builtin_fmaf(%s, -128.0f, K_%d))" % (
+                            r, r, entry(r, c), r)
                     else:
-                        sel = "__builtin_amdgcn_fmed3f(m1_%d, m2_%d, P_%d - A[%d])" % (r, r, r, c)
+                        sel = "__builtin_amdgcn_fmed3f(m1_%d, m2_%d, P_%d - %s)" % (r, r, r, entry(r, c))
                     out.append("        const float t%d_%d = %s;" % (r, k + q, sel))
                 for q, c in enumerate(pair):
                     out.append("        T[%d] = __builtin_fmaf(sg%d, t%d_%d, T[%d]);" % (c, r, r, k + q, c))
                 out.append("        __builtin_amdgcn_sched_barrier(0);")
-        out.append("    }")
+        if not lds:
+            out.append("    }")
     out.append("}")
     return "\n".join(out)
 
@@ -743,14 +844,15 @@ def generate(stage1_lib: str, out_dir: str):
         if variant == 2 and not (group and N > 64):
             raise ValueError("the small-batch variant is for nine branches and N = 127")
         ext = mode == 3
-        # every nine-branch kernel folds its shifts but the excluded one-wave ones
-        fold = FOLD_SHIFTS and regacc and B == 9 and not ext and (
-            group or pk16 or (name, rows) not in FOLD_EXCLUDE)
+        fold = FOLD_SHIFTS and regacc and B == 9 and not ext  # every nine-branch kernel
+        # the one-wave N = 127 kernels: entries of the first columns in LDS
+        lds = LDS_COLUMNS if regacc and N > 64 and not (group or pk16 or ext or mm) else 0
         dp = {63: 21, 127: 42}.get(N, N // 3)
         if ext and not (B == 1 and prec == 0 and variant == 0):
             raise ValueError("the extrinsic-message kernel is one-branch FP32")
         if not ext and mode != 1:
             raise ValueError("specialised kernels: restart mode, or one-branch extrinsic messages")
+        dual = Dual(H, len(Hs)) if lds else None
         with open(body_path, "w") as fh:
             fh.write("// generated: %s, H %d x %d, %d edges\n" % (name, M, N, int(H.sum())))
             if ext:
@@ -768,11 +870,13 @@ def generate(stage1_lib: str, out_dir: str):
                     # 8% faster than the chain once the shifts were folded
                     fh.write(_MED3U + "\n" + folded_body_source(
                         H, dp, lambda Hs: body_source_ilp(Hs, fix8=bool(prec), group=ILP_ROWS, tree=True,
-                                                                helpers=False)))
+                                                                helpers=False, lds=lds, dual=dual)))
                 elif regacc and N > 64:
-                    fh.write(body_source_ilp(H, fix8=bool(prec), group=ILP_ROWS, tree=True))
+                    fh.write(body_source_ilp(H, fix8=bool(prec), group=ILP_ROWS, tree=True, lds=lds, dual=dual))
                 else:
                     fh.write(body_source_fix8(H, regacc) if prec else body_source(H, regacc))
+            if dual:
+                fh.write("\n\n" + dual.source())
             fh.write("\n\n" + (syndrome_source_mm(Hs) if mm else syndrome_source(Hs)) + "\n")
         src_path = os.path.join(out_dir, ns + ".hip")
         with open(src_path, "w") as fh:
@@ -790,6 +894,8 @@ def generate(stage1_lib: str, out_dir: str):
                 fh.write("#define SPEC_SPLIT %d\n" % (N <= 64))
             if fold:
                 fh.write("#define SPEC_FOLD 1\n")
+            if lds:
+                fh.write("#define SPEC_LDS_COLUMNS %d\n#define SPEC_DUAL %d\n" % (lds, (dual.n + 31) // 32))
             if not (pk16 or group):
                 fh.write("#define SPEC_RESERVE %d\n" % (RESERVE if ext or B < 9 else 0))
             fh.write('#include "%s"\n' % ("nms_spec_ext.inc" if ext else "nms_spec_mm.inc" if mm else
