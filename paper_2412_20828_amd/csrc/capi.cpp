@@ -261,6 +261,13 @@ static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *co
     a.flags = flags;
     a.trace = trace;
     a.n_codes = n_codes;
+    // up to a workgroup a CU, where a frame's own time counts: four waves a type
+    // instead of one.  One frame (eight iterations) and 256, us: (127,64) 37.5
+    // and 39.6 with one, 23.1 and 25.0 with four; (127,99) 29.7, 32.0 and 22.6,
+    // 24.2; (63,36) 44.6, 45.4 and 29.5, 29.9; (63,45) 16.9, 17.5 and 15.8, 16.3.
+    // At 512 the second workgroup of a CU waits for the first: 44.5 and 46.6
+    // for (127,64), 47.6 and 56.6 for (63,36)
+    a.wide = F <= decs[0]->n_cu;
     for (int c = 0; c < n_codes; c++)
         a.tab[c] = decs[c]->rowpar;
     hipError_t e = launch_rowpar(a, decs[0]->prm.precision == BCH_FIX8, stream);
@@ -272,7 +279,7 @@ static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
 {
     const int dp = shift_period(d->N);
     RowParImage im;
-    if (rowpar_lds_bytes(d->N, d->M, dp) > kRpMaxLds || !build_rowpar(p, im))
+    if (rowpar_lds_bytes(d->N, d->M, dp, 1) > kRpMaxLds || !build_rowpar(p, im))
         return hipSuccess;
     hipError_t e = hipMalloc(&d->d_rowpar, im.data.size());
     if (e == hipSuccess)
@@ -288,6 +295,7 @@ static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
     t.hsyn = d->d_hsyn;
     t.n_rounds = im.n_rounds;
     t.n_recs = im.n_recs;
+    t.wide = im.wide;
     t.N = d->N;
     t.M = d->M;
     t.dp = dp;

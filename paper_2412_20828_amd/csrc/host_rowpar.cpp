@@ -77,11 +77,11 @@ void order_cells(std::vector<std::vector<int>> &cells, int steps, int pad)
 
 }  // namespace
 
-size_t rowpar_lds_bytes(int N, int M, int dp)
+size_t rowpar_lds_bytes(int N, int M, int dp, int waves)
 {
     const size_t ext = (size_t)((N + 2 * dp + 4) & ~3);
     const size_t us = N > kLanes ? 2 * kLanes : kLanes;
-    return 4 * 3 * ext + 8 * 3 * (size_t)(3 * M + 2) + 4 * 2 * 3 * us;
+    return 4 * 3 * waves * ext + 8 * 3 * (size_t)(3 * M + 2) + 4 * 2 * 3 * us;
 }
 
 namespace {
@@ -194,6 +194,11 @@ bool build_rowpar(const Pcm &p, RowParImage &out)
     std::vector<uint32_t> recs;
     out.n_recs = append_lists(lists, kRec, 3 * M, recs);
     out.recs = append(out.data, recs.data(), recs.size() * 4);
+    out.wide = out.n_rounds <= (N > kLanes ? 1 : 2) * kRpWide && out.n_recs <= kRpWideRecs;
+    for (int q = 0; q < out.n_rounds; q++) {
+        const uint32_t n = reinterpret_cast<const uint32_t *>(out.data.data() + out.rounds)[q];
+        out.wide = out.wide && (int)n <= (q < kRpWide ? kRpWideSteps : kRpWideSteps2);
+    }
     return true;
 }
 

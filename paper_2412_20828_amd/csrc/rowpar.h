@@ -16,6 +16,12 @@ namespace bch {
 constexpr int kRpMaxCodes = 8;   // codes of one launch (a mixed batch)
 constexpr int kRpCols = 6;       // columns of a row per table step
 constexpr int kRpRecs = 4;       // row records of a coordinate per table step
+// the smallest calls: waves of a type, and the tables whose parts its lanes hold
+// in registers (steps of a wave's first and second round, records of a coordinate)
+constexpr int kRpWide = 4;
+constexpr int kRpWideSteps = 8;
+constexpr int kRpWideSteps2 = 4;
+constexpr int kRpWideRecs = 128;
 constexpr size_t kRpMaxLds = 65536;  // LDS of one workgroup; a larger matrix does not use the kernel
 
 // One code's tables (device pointers into one allocation) and parameters.
@@ -30,6 +36,7 @@ struct RowParTab {
     int N, M, dp, msyn;
     int max_iter;
     float alpha;
+    int wide;                    // the tables fit decode_wide's registers
 };
 
 struct RowParArgs {
@@ -44,6 +51,7 @@ struct RowParArgs {
     uint8_t *flags;           // [F]
     void *trace;              // [F][max_iter][ld] float32 / int32, or null (one code only)
     int n_codes;
+    int wide;                 // kRpWide waves a type instead of one
     RowParTab tab[kRpMaxCodes];
 };
 
@@ -54,14 +62,15 @@ struct RowParImage {
     int n_rounds = 0, n_recs = 0;
     int seg[3] = {0, 0, 0};  // generic kernels: records of a coordinate in shift s (the longest list)
     int sign_words = 0;      // words of a row's message signs
+    bool wide = false;       // RowParTab::wide
 };
 
 // Tables of the nine-branch restart-mode decode of matrix p; false if an
 // offset would not fit its 16 bits.
 bool build_rowpar(const Pcm &p, RowParImage &out);
 
-// LDS bytes of one workgroup on this code
-size_t rowpar_lds_bytes(int N, int M, int dp);
+// LDS bytes of one workgroup on this code, with `waves` waves a type
+size_t rowpar_lds_bytes(int N, int M, int dp, int waves);
 
 // ---- generic decoder (k_rowgen.hip): any matrix, 1, 3 or 9 branches, all
 // message modes.  The sums run over the shifts, then the types, so a
