@@ -350,7 +350,7 @@ def _forward(cols):
 
 
 def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: bool = True,
-                    helpers: bool = True, lds: int = 0, dual=None) -> str:
+                    helpers: bool = True, lds: int = 0, dual=None, opaque: bool = False) -> str:
     """The row function (accumulating form, FP32 or fixed point) with
     independent work side by side, for kernels that run one wave per SIMD and
     so have no other wave to issue while an instruction waits for its
@@ -366,13 +366,14 @@ def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: boo
     through a pointer made opaque per row (else equal loads of all rows merge,
     and the values fill the registers they were to free).
 
-    dual: S holds the bits of Dual instead of the sign words."""
+    dual: S holds the bits of Dual instead of the sign words.  opaque: A opaque
+    per row, so that rows share no partial minima."""
     M, N = H.shape
     if lds and group != 1:
         raise ValueError("columns in LDS: one row at a time")
     out = ([_MED3U] if helpers else []) + ["__device__ __forceinline__ void body(%sfloat *__restrict__ A, %s"
                                            "const uint32_t *__restrict__ S, float *__restrict__ T)"
-                                           % (("", "LdsColumns AL, ") if lds else ("const ", "")), "{"]
+                                           % ("" if opaque else "const ", "LdsColumns AL, " if lds else ""), "{"]
 
     def fetch(j):
         low = [int(c) for c in np.nonzero(H[j])[0] if c < lds]
@@ -400,7 +401,7 @@ def body_source_ilp(H: np.ndarray, fix8: bool = False, group: int = 1, tree: boo
             out.append("        const float sg%d = __uint_as_float(0x3f800000u | ((%s) << 31));" % (r, cnt))
         steps = {r: _min_steps(cols[r], "_%d" % r, lambda c, r=r: "__float_as_uint(%s)" % entry(r, c), tree=tree)
                  for r in cols}
-        if lds:
+        if opaque:
             out += ['        __asm__("" : "+v"(A[%d]));' % c for r in cols for c in cols[r] if c >= lds]
         for k in range(max(len(st) for st in steps.values())):
             for r in cols:
@@ -852,7 +853,7 @@ def generate(stage1_lib: str, out_dir: str):
             raise ValueError("the extrinsic-message kernel is one-branch FP32")
         if not ext and mode != 1:
             raise ValueError("specialised kernels: restart mode, or one-branch extrinsic messages")
-        dual = Dual(H, len(Hs)) if lds else None
+        dual = Dual(H, len(Hs)) if lds or (group and N <= 64) else None
         with open(body_path, "w") as fh:
             fh.write("// generated: %s, H %d x %d, %d edges\n" % (name, M, N, int(H.sum())))
             if ext:
@@ -865,14 +866,15 @@ def generate(stage1_lib: str, out_dir: str):
                 fh.write(body_source_pk16(H, B))
             else:
                 if fold:
-                    # the triple search; in the grouped N = 63 kernels its extra
-                    # live values spill some registers, and it still measured
-                    # 8% faster than the chain once the shifts were folded
+                    # the triple search, 8% faster than the chain in the grouped
+                    # N = 63 kernels too once the shifts were folded
                     fh.write(_MED3U + "\n" + folded_body_source(
                         H, dp, lambda Hs: body_source_ilp(Hs, fix8=bool(prec), group=ILP_ROWS, tree=True,
-                                                                helpers=False, lds=lds, dual=dual)))
+                                                                helpers=False, lds=lds, dual=dual,
+                                                                opaque=dual is not None)))
                 elif regacc and N > 64:
-                    fh.write(body_source_ilp(H, fix8=bool(prec), group=ILP_ROWS, tree=True, lds=lds, dual=dual))
+                    fh.write(body_source_ilp(H, fix8=bool(prec), group=ILP_ROWS, tree=True, lds=lds, dual=dual,
+                                             opaque=dual is not None))
                 else:
                     fh.write(body_source_fix8(H, regacc) if prec else body_source(H, regacc))
             if dual:
@@ -895,7 +897,9 @@ def generate(stage1_lib: str, out_dir: str):
             if fold:
                 fh.write("#define SPEC_FOLD 1\n")
             if lds:
-                fh.write("#define SPEC_LDS_COLUMNS %d\n#define SPEC_DUAL %d\n" % (lds, (dual.n + 31) // 32))
+                fh.write("#define SPEC_LDS_COLUMNS %d\n" % lds)
+            if dual:
+                fh.write("#define SPEC_DUAL %d\n" % ((dual.n + 31) // 32))
             if not (pk16 or group):
                 fh.write("#define SPEC_RESERVE %d\n" % (RESERVE if ext or B < 9 else 0))
             fh.write('#include "%s"\n' % ("nms_spec_ext.inc" if ext else "nms_spec_mm.inc" if mm else

@@ -1,5 +1,6 @@
-"""The one-wave kernels of N = 127 on calls of many frames a lane against the
-row-parallel kernel on the same frames in small calls, bit for bit."""
+"""The one-wave kernels of N = 127 and the grouped ones of N = 63 on calls of
+many frames a lane against the row-parallel kernel on the same frames in small
+calls, bit for bit."""
 import numpy as np
 import pytest
 
@@ -18,8 +19,8 @@ def B():
     return b
 
 
-@pytest.mark.parametrize("F,ebn0", [(40_001, 1.0), (150_000, 4.0)])
-@pytest.mark.parametrize("name", ["bch127_64", "bch127_78", "bch127_99"])
+@pytest.mark.parametrize("F,ebn0", [(60_001, 1.0), (150_000, 4.0)])
+@pytest.mark.parametrize("name", ["bch127_64", "bch127_78", "bch127_99", "bch63_36", "bch63_45"])
 def test_equals_small_calls(B, name, F, ebn0):
     d = B.CODE_DEFS[name]
     c = B.Code(d.m, d.prim, d.t)
@@ -28,8 +29,9 @@ def test_equals_small_calls(B, name, F, ebn0):
     fr = synth.frames(name, 20_000, ebn0, seed=51)
     rep = -(-F // 20_000)
     llr = torch.from_numpy(fr.llr).cuda().repeat(rep, 1)[:F].contiguous()
-    d_o = torch.from_numpy(np.random.default_rng(5).integers(0, 42, F, dtype=np.uint8)).cuda()
-    trace = F < 50_000
+    d_o = torch.from_numpy(np.random.default_rng(5).integers(0, B.shift_period(c.N), F,
+                                                              dtype=np.uint8)).cuda()
+    trace = F < 70_000
     big = dec.decode(llr, d_o, trace=trace)
     n = 16_384
     for f0 in range(0, F, n):
