@@ -213,7 +213,9 @@ int bch_decoder_is_specialized(bch_decoder dec);
  * lane-per-frame kernel it stands in for.  So it is with the fixed-point kernel
  * whose sums run on the matrix cores, in decoders without those three flags:
  * (127,64) with 72 and (127,99) with 33 rows from 96 frames per CU on (the
- * row-parallel kernel's limit there), (63,36) with 122 rows from 2400. */
+ * row-parallel kernel's limit there), (63,36) with 122 rows from 2400.
+ * Specialised one-branch decoders without the two SMALL flags run calls of up
+ * to 64 frames per CU on the generic kernel's frame-per-workgroup form. */
 const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F);
 void bch_decoder_destroy(bch_decoder dec);
 

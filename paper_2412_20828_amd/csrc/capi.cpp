@@ -274,6 +274,17 @@ static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *co
     return e == hipSuccess ? BCH_OK : hip_fail(e, "row-parallel kernel launch");
 }
 
+// Largest call of the generic frame-per-workgroup kernel (k_rowgen.hip) in the
+// place of a specialised one-branch kernel, whose bits it gives.  Measured in us
+// per call at 2 / 4.5 dB, this kernel against the specialised one, 12
+// iterations, standard matrices:
+//   (63,36)  300: 40 / 40, 199 / 199   10000: 117 / 75, 206 / 207
+//            20000: 197 / 108, 213 / 214   40000: 351 / 176, 231 / 232
+//   (63,45)  300: 47 / 47, 179 / 180   10000: 133 / 83, 188 / 187
+//            20000: 220 / 112, 196 / 194
+// hence 64 frames per CU
+static int64_t rowgen_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * 64; }
+
 // device copy of a decoder's row-parallel tables
 static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
 {
@@ -763,7 +774,9 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
     }
     d->fingerprint = pcm_fingerprint(p);
     try {
-        if (!d->spec && q.precision == BCH_FP32)
+        const bool lanes = q.flags & (BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER);  // lane-per-frame kernels only
+        if (q.precision == BCH_FP32 &&
+            (!d->spec || (q.n_branches == 1 && q.mode == BCH_MODE_EXTRINSIC && !lanes)))
             he = make_rowgen(d, p);
         else if (d->spec && q.n_branches == 9 && q.mode == BCH_MODE_RESTART &&
                  !(q.flags & (BCH_DEC_PACKED16 | BCH_DEC_SMALL_ALWAYS | BCH_DEC_SMALL_NEVER)))
@@ -853,7 +866,7 @@ int bch_nms_decode_batch(bch_decoder dec, const void *llr, int64_t ld, int64_t F
         return fail(BCH_EINVAL, "decoder belongs to another device");
     if (dec->d_rowpar && F <= rowpar_max_frames(dec))
         return rowpar_decode(&dec, 1, nullptr, llr, ld, F, d_o, bits, dec->W64, iters, flags, y_trace, stream);
-    if (dec->spec)
+    if (dec->spec && !(dec->d_rowgen && F <= rowgen_max_frames(dec)))
         return spec_decode(dec, llr, ld, F, d_o, nullptr, 0, bits, dec->W64, iters, flags, y_trace, workspace,
                            stream);
     GenericArgs a{};
