@@ -2,9 +2,9 @@
 // random cyclic offset d_o so that a wave's 64 frames share every branch
 // permutation.  Counting sort without global atomics:
 //   1. each block of BLK frames counts its frames per bucket;
-//   2. one workgroup scans the per-block counts bucket by bucket (bucket
-//      starts, per-block offsets, bucket slices [cursor, end));
-//   3. each block places its frames at its offsets plus their rank inside the
+//   2. a workgroup per bucket scans its per-block counts (per-block offsets, total);
+//   3. each block sums the totals (bucket starts; the first block writes the bucket
+//      slices [cursor, end)) and places its frames at its offsets plus their rank inside the
 //      block (LDS counters).
 // Frames keep their input order inside a (block, bucket) up to the LDS-atomic
 // ranks; no result depends on that order (every frame is decoded on its own).
@@ -23,7 +23,7 @@ namespace {
 constexpr int MAXB = 512;
 constexpr int BLK = 2048;   // frames per counting block
 constexpr int TPB = 256;    // threads per counting block
-constexpr int SCAN = 1024;  // threads of the scan workgroup
+constexpr int SCAN = 1024;  // threads of a scan workgroup
 
 // which frames go to which bucket: one code (code_idx null, or the frames
 // with code_idx == code), bucket (f ranges / F) nofs + d_o mod dp (offset 0
@@ -72,56 +72,68 @@ __global__ void __launch_bounds__(TPB) bucket_count(const uint8_t *__restrict__ 
         blk_hist[(size_t)blockIdx.x * nb + i] = h[i];
 }
 
-// one workgroup: per-block offsets in bucket-major order, bucket slices
-__global__ void __launch_bounds__(SCAN) bucket_scan(int *__restrict__ blk_hist, int nblk, int dp, BucketWs w)
+// inclusive prefix over a wave's lanes
+__device__ __forceinline__ int wave_prefix(int v, int lane)
 {
-    __shared__ int bucket_total[MAXB];
-    __shared__ int bucket_start[MAXB];
-    const int tid = threadIdx.x;
-    // one wave per bucket: exclusive prefix over the blocks, 64 blocks at a
-    // time with a shuffle scan (no workgroup barriers inside)
-    const int lane = tid & 63, wave = tid >> 6;
-    for (int d = wave; d < dp; d += SCAN / 64) {
-        int carry = 0;
-        for (int b0 = 0; b0 < nblk; b0 += 64) {
-            const int b = b0 + lane;
-            const int c = b < nblk ? blk_hist[(size_t)b * dp + d] : 0;
-            int v = c;
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(v, off);
-                if (lane >= off)
-                    v += t;
-            }
-            if (b < nblk)
-                blk_hist[(size_t)b * dp + d] = carry + v - c;  // offset inside the bucket
-            carry += __shfl(v, 63);
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(v, off);
+        if (lane >= off)
+            v += t;
+    }
+    return v;
+}
+
+// a workgroup per bucket: offsets of the blocks inside it, and its total.
+// Latency bounds it: one workgroup for all buckets, 64 blocks of one a step,
+// took 88 and 165 us at 4 and 7 million frames; 1024 blocks a step and the
+// buckets side by side take 5 and 9
+__global__ void __launch_bounds__(SCAN) bucket_scan(int *__restrict__ blk_hist, int nblk, int nb, BucketWs w)
+{
+    __shared__ int sums[2][SCAN / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = blockIdx.x;
+    int carry = 0, turn = 0;
+    for (int b0 = 0; b0 < nblk; b0 += SCAN, turn ^= 1) {
+        const int b = b0 + tid;
+        const int c = b < nblk ? blk_hist[(size_t)b * nb + d] : 0;
+        const int v = wave_prefix(c, lane);
+        if (lane == 63)
+            sums[turn][wave] = v;
+        __syncthreads();
+        int before = carry;
+#pragma unroll
+        for (int k = 0; k < SCAN / 64; k++) {
+            before += k < wave ? sums[turn][k] : 0;
+            carry += sums[turn][k];
         }
-        if (lane == 0)
-            bucket_total[d] = carry;
+        if (b < nblk)
+            blk_hist[(size_t)b * nb + d] = before + v - c;
     }
-    __syncthreads();
-    if (tid == 0) {
-        int start = 0;
-        for (int d = 0; d < dp; d++) {
-            bucket_start[d] = start;
-            start += bucket_total[d];
-        }
-    }
-    __syncthreads();
-    if (tid < dp) {
-        w.counts[tid] = bucket_total[tid];
-        w.cursor[tid] = bucket_start[tid];
-        w.end[tid] = bucket_start[tid] + bucket_total[tid];
-    }
+    if (tid == 0)
+        w.counts[d] = carry;
 }
 
 __global__ void __launch_bounds__(TPB) bucket_place(const uint8_t *__restrict__ d_o, BucketMap m, int64_t F,
                                                     int nb, const int *__restrict__ blk_off, BucketWs w)
 {
     __shared__ int h[MAXB];
-    for (int i = threadIdx.x; i < nb; i += TPB)
-        h[i] = w.cursor[i] + blk_off[(size_t)blockIdx.x * nb + i];
+    // bucket starts: every block sums the totals, the first one writes the slices
+    if (threadIdx.x < 64) {
+        int start = 0;
+        for (int i0 = 0; i0 < nb; i0 += 64) {
+            const int i = i0 + threadIdx.x;
+            const int c = i < nb ? w.counts[i] : 0;
+            const int v = wave_prefix(c, threadIdx.x);
+            if (i < nb) {
+                h[i] = start + v - c + blk_off[(size_t)blockIdx.x * nb + i];
+                if (blockIdx.x == 0) {
+                    w.cursor[i] = start + v - c;
+                    w.end[i] = start + v;
+                }
+            }
+            start += __shfl(v, 63);
+        }
+    }
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * BLK;
     for (int k = threadIdx.x; k < BLK; k += TPB) {
@@ -171,7 +183,7 @@ static hipError_t run_bucketing(const uint8_t *d_o, const BucketMap &m, int64_t 
         return hipErrorInvalidValue;
     const int nblk = (int)n_blocks(F);
     hipLaunchKernelGGL(bucket_count, dim3(nblk), dim3(TPB), 0, stream, d_o, m, F, nb, w.blk_hist);
-    hipLaunchKernelGGL(bucket_scan, dim3(1), dim3(SCAN), 0, stream, w.blk_hist, nblk, nb, w);
+    hipLaunchKernelGGL(bucket_scan, dim3(nb), dim3(SCAN), 0, stream, w.blk_hist, nblk, nb, w);
     hipLaunchKernelGGL(bucket_place, dim3(nblk), dim3(TPB), 0, stream, d_o, m, F, nb, w.blk_hist, w);
     return hipGetLastError();
 }
