@@ -129,7 +129,7 @@ def running_kernel(dec, B, F):
     if base in MM_KERNELS and not dec.flags & (B.PACKED16 | B.SMALL_ALWAYS | B.SMALL_NEVER):
         import torch
         n_cu = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
-        if F > 96 * n_cu if dec.N > 64 else F >= 2400 * n_cu:
+        if F > 92 * n_cu if dec.N > 64 else F >= 2400 * n_cu:
             return base + "_mm"
     return name
 

@@ -165,8 +165,9 @@ enum {
     BCH_DEC_SMALL_ALWAYS = 4,  /* N = 127: always use the small-batch kernel (the nine
                                   branches of 64 frames on three waves) where registered */
     BCH_DEC_SMALL_NEVER = 8,   /* N = 127: never use it.  Without either flag a decode of at
-                                  most 128 frames per CU runs the row-parallel kernel, a
-                                  larger one the kernel of one wave per 64 frames; either
+                                  most 92 frames per CU runs the row-parallel kernel, FP32
+                                  ones of up to 128 per CU this one, a larger one the kernel
+                                  of one wave per 64 frames; either
                                   flag also excludes the row-parallel kernel and the one with
                                   its sums on the matrix cores (both code lengths); the
                                   results are the same.
@@ -207,13 +208,13 @@ int bch_decoder_is_specialized(bch_decoder dec);
  * generic kernel, "" for a null decoder); the string is static and owned by
  * the library.  Nine-branch restart-mode decoders without BCH_DEC_PACKED16,
  * BCH_DEC_SMALL_ALWAYS or BCH_DEC_SMALL_NEVER run small calls (N = 127: up to
- * 128 frames per CU, N = 63: 224, a mixed-code call without either of its
+ * 92 frames per CU, N = 63: 224, a mixed-code call without either of its
  * flags: 256) on the row-parallel kernel instead, a frame per workgroup in one
  * launch, with the same results bit for bit; the name is that of the
  * lane-per-frame kernel it stands in for.  So it is with the fixed-point kernel
  * whose sums run on the matrix cores, in decoders without those three flags:
- * (127,64) with 72 and (127,99) with 33 rows from 96 frames per CU on (the
- * row-parallel kernel's limit there), (63,36) with 122 rows from 2400.
+ * (127,64) with 72 and (127,99) with 33 rows from 92 frames per CU on (the
+ * row-parallel kernel's limit), (63,36) with 122 rows from 2400.
  * Specialised one-branch decoders without the two SMALL flags run calls of up
  * to 64 frames per CU on the generic kernel's frame-per-workgroup form. */
 const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F);

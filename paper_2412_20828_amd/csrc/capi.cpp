@@ -221,26 +221,25 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
 // the frame-iterations from the first frame on; the lane-per-frame kernels
 // take the time of their slowest frame's iterations up to about 64 frames per
 // CU and stop early only frame by frame.  Measured in us per call, row-parallel
-// against the kernel it replaces, at 2 dB (hardest case, 3.0-7.6 iterations a
-// frame) and 3 dB, on 256 CUs:
-//   N = 127, 72 rows  16384: 711 / 773, 518 / 603   32768: 1193 / 1227, 946 / 996
-//                     40960: 1412 / 1306
-//   N = 127, 33 rows  16384: 567 / 661, 388 / 473   32768: 1031 / 1027, 737 / 814
-//   N = 63, 122 rows  32768: 650 / 939, 349 / 924   49152: 866 / 1074, 486 / 1069
-//                     65536: 1110 / 1115, 629 / 1105 (fixed point 1202 / 1169)
-//   N = 63, 33 rows   32768: 192 / 306, 122 / 300   65536: 348 / 370, 222 / 366
-// hence 128 frames per CU for N > 64 and 224 for N <= 64.  Against the kernel
-// with its sums on the matrix cores (fixed point, N = 127, 72 rows; about 730
-// at each of these sizes and Eb/N0) it takes, at 2 / 3 / 5 dB,
-//   16384: 704 / 575 / 191   24576: 968 / 794 / 255   32768: 1233 / 1029 / 334
-// hence 96 frames per CU there.  A mixed-code call of
-// the service's four codes takes 899 / 1450 us at 32768 frames, 1684 / 1731 at
-// 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455 at 65536 over 2-5 dB):
-// 256 per CU.
-static int64_t rowpar_max_frames(const bch_decoder_s *d)
-{
-    return (int64_t)d->n_cu * (d->N <= 64 ? 224 : d->spec_mm ? 96 : 128);
-}
+// against the kernel that takes the call otherwise, at 2 / 3 / 5 dB (2 dB the
+// hardest case, 3.0-7.6 iterations a frame), on 256 CUs:
+//   N = 127, 72 rows  16384: 676 / 545 / -, 888 / 618 / -
+//                     24576: 949 / 771 / 241, 918 / 912 / 574
+//                     28672: 1086 / 875 / 279, 925 / 922 / 583
+//   N = 127, 33 rows  24576: 788 / 610 / 171, 809 / 800 / 467
+//                     28672: 907 / 720 / 203, 814 / 808 / 507
+//   N = 63, 122 rows  49152: 900 / 503 / -, 1017 / 997 / -
+//                     57344: 996 / 581 / 304, 1007 / 1008 / 621
+//   N = 63, 33 rows   49152: 279 / 176 / -, 330 / 325 / -
+//                     57344: 321 / 197 / 120, 338 / 335 / 210
+// hence 92 frames per CU for N > 64 and 224 for N <= 64, where no Eb/N0 loses.
+// Fixed point, N = 127, 72 rows, against the kernel with its sums on the matrix
+// cores (about 690 at any of these sizes and Eb/N0):
+//   20480: 862 / 704 / 235   24576: 993 / 830 / 268
+// A mixed-code call of the service's four codes takes 899 / 1450 us at 32768
+// frames, 1684 / 1731 at 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455
+// at 65536 over 2-5 dB): 256 per CU.
+static int64_t rowpar_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * (d->N > 64 ? 92 : 224); }
 static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
 
 // one launch of the row-parallel kernel: frame f with decs[code_idx[f]] (or

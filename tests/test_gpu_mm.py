@@ -30,9 +30,9 @@ def make(B, name, **kw):
 
 def smallest(name):
     """Frames of the kernel's smallest call: the row-parallel kernel takes those
-    up to 96 per CU of N = 127, the waves of N = 63 those up to 2400."""
+    up to 92 per CU of N = 127, the waves of N = 63 those up to 2400."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    return n_cu * 96 + 1 if name.startswith("bch127") else n_cu * 2400
+    return n_cu * 92 + 1 if name.startswith("bch127") else n_cu * 2400
 
 
 def frames(name, F, ebn0, seed):
