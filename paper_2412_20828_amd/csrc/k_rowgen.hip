@@ -37,6 +37,8 @@
 // the shifts first, so only the coordinates can be spread there.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "rowpar.h"
 
@@ -379,16 +381,31 @@ void launch(const GenericArgs &a, const RowGenTab &t, size_t lds, hipStream_t st
 
 }  // namespace
 
-hipError_t launch_rowgen(const GenericArgs &a, const RowGenTab &t, hipStream_t stream)
+hipError_t launch_rowgen(const GenericArgs &args, const RowGenTab &t, hipStream_t stream)
 {
-    const size_t lds = rowgen_lds_bytes(t, a.N, a.M, a.mode);
-    if (a.F < 1 || a.F > (int64_t)0x7fffffff || lds > kRpMaxLds || a.msyn > 2 * WAVE)
+    const size_t lds = rowgen_lds_bytes(t, args.N, args.M, args.mode);
+    if (args.F < 1 || lds > kRpMaxLds || args.msyn > 2 * WAVE)
         return hipErrorInvalidValue;
-    if (a.N > WAVE)
-        launch<2>(a, t, lds, stream);
-    else
-        launch<1>(a, t, lds, stream);
-    return hipGetLastError();
+    // a dispatch counts its work-items, 64 or 128 a frame, in 32 bits: more
+    // frames take several launches
+    GenericArgs a = args;
+    for (int64_t done = 0; done < args.F; done += a.F) {
+        a.F = std::min(args.F - done, (int64_t)kRgLaunchFrames);
+        a.llr = static_cast<const float *>(args.llr) + done * args.ld;
+        a.d_o = args.d_o ? args.d_o + done : nullptr;
+        a.bits = args.bits + done * args.W64;
+        a.iters = args.iters + done;
+        a.flags = args.flags + done;
+        a.trace = args.trace ? args.trace + done * args.max_iter * args.ld_trace : nullptr;
+        if (a.N > WAVE)
+            launch<2>(a, t, lds, stream);
+        else
+            launch<1>(a, t, lds, stream);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace bch

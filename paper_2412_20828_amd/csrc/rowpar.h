@@ -79,6 +79,7 @@ size_t rowpar_lds_bytes(int N, int M, int dp, int waves);
 // state | the entry's position in the row << 16 | (32 word + bit) << 24 of the
 // position's sign.
 constexpr int kRgSigns = 30;  // positions (five table steps) whose signs share a word
+constexpr int kRgLaunchFrames = 1 << 24;  // frames of one launch (below 2^32 work-items of 128 threads a frame)
 
 struct RowGenTab {
     const uint32_t *steps;
