@@ -320,6 +320,9 @@ static hipError_t make_rowgen(bch_decoder_s *d, const Pcm &p)
 {
     const bool memory = d->prm.mode != BCH_MODE_RESTART;
     RowParImage im;
+    // an infinite or NaN alpha makes a NaN of the zero records past a list's end
+    if (!memory && !std::isfinite(d->prm.alpha))
+        return hipSuccess;
     if (!build_rowgen(p, d->prm.n_branches, memory, im))
         return hipSuccess;
     RowGenTab t{};

@@ -302,7 +302,8 @@ __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenT
                                 // row sign and magnitude; the sign of y_u comes in below
                                 const float s1 = __uint_as_float(rc[e].x), m1 = fabsf(s1);
                                 const float am = A.alpha * (a == m1 ? __uint_as_float(rc[e].y) : m1);
-                                T += __builtin_copysignf(am, s1);
+                                // alpha may be negative: flip, not set, the sign
+                                T += __uint_as_float(__float_as_uint(am) ^ (__float_as_uint(s1) & 0x80000000u));
                             }
                         };
                         const int whole = cnt / kRpRecs;
