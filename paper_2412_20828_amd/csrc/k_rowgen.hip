@@ -138,7 +138,9 @@ __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenT
                 words[wv] = w;
             if (in)
                 for (int p = 0; p < np; p++) {
-                    const float e = MEM ? y : fabsf(y);
+                    // a NaN is no minimum of its rows and no least entry, as +inf is;
+                    // the medians of the search would return one of the others for it
+                    const float e = MEM ? y : fminf(fabsf(y), __builtin_inff());
                     float *dst = E + p * ext_pad + kp[p];
                     dst[(ns - 1) * dp] = e;
                     if (kp[p] >= N - (ns - 1) * dp)
