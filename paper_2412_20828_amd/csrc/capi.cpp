@@ -315,7 +315,8 @@ static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
     return hipSuccess;
 }
 
-// device copy of a generic decoder's row-parallel tables
+// device copy of the frame-per-workgroup kernel's tables, of a generic decoder or
+// one with a specialised one-branch kernel, in whose place it runs small calls
 static hipError_t make_rowgen(bch_decoder_s *d, const Pcm &p)
 {
     const bool memory = d->prm.mode != BCH_MODE_RESTART;
@@ -323,7 +324,13 @@ static hipError_t make_rowgen(bch_decoder_s *d, const Pcm &p)
     // an infinite or NaN alpha makes a NaN of the zero records past a list's end
     if (!memory && !std::isfinite(d->prm.alpha))
         return hipSuccess;
-    if (!build_rowgen(p, d->prm.n_branches, memory, im))
+    // a stand-in has the specialised kernel's result for posteriors of any kind:
+    // its rows are of one sign word, and that kernel sets signs where this one
+    // flips them, which differ for alpha < 0 and on the NaN of 0 inf
+    const bool ordered = d->spec != nullptr;
+    if (ordered && !(d->N <= 64 && d->prm.n_branches == 1 && d->prm.alpha > 0.0f && std::isfinite(d->prm.alpha)))
+        return hipSuccess;
+    if (!build_rowgen(p, d->prm.n_branches, memory, ordered, im) || (ordered && im.sign_words != 1))
         return hipSuccess;
     RowGenTab t{};
     t.n_rounds = im.n_rounds;
@@ -346,6 +353,7 @@ static hipError_t make_rowgen(bch_decoder_s *d, const Pcm &p)
     t.mask = reinterpret_cast<const uint4 *>(d->d_rowgen + im.mask);
     t.slot = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.slot);
     t.recs = reinterpret_cast<const uint32_t *>(d->d_rowgen + im.recs);
+    t.order = ordered ? d->d_rowgen + im.order : nullptr;
     d->rowgen = t;
     return hipSuccess;
 }

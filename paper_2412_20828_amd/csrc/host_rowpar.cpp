@@ -89,7 +89,9 @@ namespace {
 // Rounds of 64 rows (s, r), s < ns: steps, masks and record slots.  stride:
 // bytes of a record; where: if not null, receives each row's columns in the
 // order read, [s * M + r][position] (the pad cell for a lane that sits out).
-void build_rounds(const Pcm &p, int ns, int dp, int stride, RowParImage &out, std::vector<std::vector<int>> *where)
+// ordered (one branch): also the positions of a row's columns, ascending.
+void build_rounds(const Pcm &p, int ns, int dp, int stride, bool ordered, RowParImage &out,
+                  std::vector<std::vector<int>> *where)
 {
     const int N = p.N, M = p.M;
     const int ext = N + (ns - 1) * dp;  // cells of a type's extended input; cell ext is the pad (+inf)
@@ -104,6 +106,7 @@ void build_rounds(const Pcm &p, int ns, int dp, int stride, RowParImage &out, st
     std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.w > b.w; });
     const int R = (int)(items.size() + kLanes - 1) / kLanes;
     std::vector<uint32_t> steps, rounds, mask, slot;
+    std::vector<uint8_t> order;
     if (where)
         where->assign(ns * M, {});
     for (int q = 0; q < R; q++) {
@@ -136,6 +139,16 @@ void build_rounds(const Pcm &p, int ns, int dp, int stride, RowParImage &out, st
                     const uint32_t b = 4u * cells[l][e * kRpCols + 2 * h + 1];
                     steps.push_back(a | (b << 16));
                 }
+        for (int k = 0; ordered && k < n * kRpCols; k++)
+            for (int l = 0; l < kLanes; l++) {
+                std::vector<int> c;
+                for (int x : cells[l])
+                    if (x != ext)
+                        c.push_back(x);
+                std::sort(c.begin(), c.end());
+                const bool in = k < (int)c.size();
+                order.push_back(in ? (uint8_t)(std::find(cells[l].begin(), cells[l].end(), c[k]) - cells[l].begin()) : 0);
+            }
         rounds.push_back((uint32_t)n);
         out.sign_words = std::max(out.sign_words, (n * kRpCols + kRgSigns - 1) / kRgSigns);
         if (where)
@@ -150,6 +163,8 @@ void build_rounds(const Pcm &p, int ns, int dp, int stride, RowParImage &out, st
     out.rounds = append(out.data, rounds.data(), rounds.size() * 4);
     out.mask = append(out.data, mask.data(), mask.size() * 4);
     out.slot = append(out.data, slot.data(), slot.size() * 4);
+    if (ordered)
+        out.order = append(out.data, order.data(), order.size());
     out.n_rounds = R;
 }
 
@@ -183,7 +198,7 @@ bool build_rowpar(const Pcm &p, RowParImage &out)
     if (kRec * (3 * M + 2) > 65535)
         return false;
     out = RowParImage();
-    build_rounds(p, 3, dp, kRec, out, nullptr);
+    build_rounds(p, 3, dp, kRec, false, out, nullptr);
     // records of coordinate k in the order of the sums: shift 0's rows, 1's, 2's
     std::vector<std::vector<int>> lists(N > kLanes ? 2 * kLanes : kLanes);
     for (int k = 0; k < N; k++)
@@ -207,7 +222,7 @@ int rowgen_stride(const RowParImage &im, bool memory)
     return memory ? 4 * ((3 + im.sign_words + 1) & ~1) : 8;
 }
 
-bool build_rowgen(const Pcm &p, int n_branches, bool memory, RowParImage &out)
+bool build_rowgen(const Pcm &p, int n_branches, bool memory, bool ordered, RowParImage &out)
 {
     const int N = p.N, M = p.M, ns = n_branches > 1 ? 3 : 1, dp = n_branches > 1 ? shift_period(N) : 0;
     out = RowParImage();
@@ -220,7 +235,7 @@ bool build_rowgen(const Pcm &p, int n_branches, bool memory, RowParImage &out)
     if ((long)stride * (ns * M + 2) > 65535)
         return false;
     std::vector<std::vector<int>> where;
-    build_rounds(p, ns, dp, stride, out, &where);
+    build_rounds(p, ns, dp, stride, ordered, out, &where);
     const int n = N > kLanes ? 2 * kLanes : kLanes;
     std::vector<uint32_t> recs;
     for (int s = 0; s < ns; s++) {

@@ -41,16 +41,12 @@
 
 #include "kernels.h"
 #include "rowpar.h"
+#include "rowsearch.h"
 
 namespace bch {
 namespace {
 
 constexpr int WAVE = 64;
-
-__device__ __forceinline__ uint32_t med3i(uint32_t a, uint32_t b, uint32_t c)
-{
-    return __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(a), __uint_as_float(b), __uint_as_float(c)));
-}
 
 // all LDS traffic of the workgroup before this point is seen after it
 template <int NK>
@@ -77,7 +73,49 @@ __device__ __forceinline__ int times(int p, int x, int N)
     return p == 0 ? x : (p == 1 ? dbl : hlf);
 }
 
-template <int NK, int MODE>
+// Extrinsic messages of a one-branch decoder that stands in for a specialised
+// kernel: a row's entries in the order of that kernel (nms_spec_ext.inc), its
+// signs the sign bits and its argmin the last entry equal to the least, as there.
+// n <= 5 table steps from sp, ord: the position of the row's k-th column at [k][lane].
+__device__ __forceinline__ void ordered_row(const StepWord *sp, const uint8_t *ord, int n, int w, int lane, const char *Eb,
+                                            float alpha, char *rec)
+{
+    const float a1 = reinterpret_cast<const float *>(rec)[0], a2 = reinterpret_cast<const float *>(rec)[1];
+    const uint32_t arg = reinterpret_cast<const uint32_t *>(rec)[2], old = reinterpret_cast<const uint32_t *>(rec)[3];
+    const int last = kRpCols * n - 1;
+    // v of the row's k-th column, at position e
+    auto entry = [&](int k, int &e) {
+        e = ord[k * WAVE + lane];
+        const uint32_t st = reinterpret_cast<const uint32_t *>(sp + (e / kRpCols) * WAVE + lane)[e % kRpCols / 2];
+        const float own = (uint32_t)e == arg ? a2 : a1;
+        const float y = *reinterpret_cast<const float *>(Eb + (e & 1 ? st >> 16 : st & 0xffffu));
+        return y - __uint_as_float(__float_as_uint(own) ^ ((old >> (last - e)) << 31));
+    };
+    int k = 0;
+    uint32_t ng = 0u;
+    const uint2 u = ordered_search(w, [&]() {
+        int e;
+        const uint32_t v = __float_as_uint(entry(k++, e));
+        ng |= (v >> 31) << (last - e);
+        return v & 0x7fffffffu;
+    });
+    uint32_t at = 0xffu;
+#pragma unroll 1
+    for (k = 0; k < w; k++) {
+        int e;
+        if ((__float_as_uint(entry(k, e)) & 0x7fffffffu) == u.x)
+            at = (uint32_t)e;
+    }
+    const uint32_t par = (uint32_t)__builtin_popcount(ng) << 31;
+    reinterpret_cast<uint32_t *>(rec)[0] = __float_as_uint(alpha * __uint_as_float(u.x)) ^ par;
+    reinterpret_cast<uint32_t *>(rec)[1] = __float_as_uint(alpha * __uint_as_float(u.y)) ^ par;
+    reinterpret_cast<uint32_t *>(rec)[2] = at;
+    reinterpret_cast<uint32_t *>(rec)[3] = ng;
+}
+
+// ORD: extrinsic messages in the place of a specialised kernel; a kernel of its
+// own, as the ordered search takes registers
+template <int NK, int MODE, bool ORD>
 __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenTab tb)
 {
     extern __shared__ __align__(16) char lds[];
@@ -133,7 +171,9 @@ __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenT
     for (int t = 0;; t++) {
         // ---- 1. signs and inputs; syndrome and end of the frame
         {
-            const uint64_t w = __ballot(in && y < 0.0f);
+            // the specialised kernels decide on the sign bit, of a NaN too
+            const uint64_t w = __ballot(in && (ORD ? (int)__float_as_uint(y) < 0 : y < 0.0f));
+            const bool odd_frame = ORD && __ballot(in && !(fabsf(y) < __builtin_inff())) != 0ull;
             if (NK > 1 && lane == 0)
                 words[wv] = w;
             if (in)
@@ -195,6 +235,16 @@ __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenT
                         continue;
                     }
                     char *rec = Rp + tb.slot[q * WAVE + lane];
+                    if constexpr (ORD) {
+                        if (odd_frame) {
+                            const uint4 mk = tb.mask[q * WAVE + lane];
+                            const size_t step = sp - reinterpret_cast<const StepWord *>(tb.steps);  // WAVE words a step
+                            ordered_row(sp, tb.order + kRpCols * step, n, __popc(mk.x) + __popc(mk.y), lane, Eb, A.alpha,
+                                        rec);
+                            sp += n * WAVE;
+                            continue;
+                        }
+                    }
                     StepWord nx = sp[lane];
                     if constexpr (!MEM) {
                         const uint4 mk = tb.mask[q * WAVE + lane];
@@ -352,7 +402,7 @@ __global__ void __launch_bounds__(NK *WAVE) rowgen_decode(GenericArgs A, RowGenT
                 list += MEM ? (cnt + 1) * n : (cnt + kRpRecs - 1) / kRpRecs * 2 * n + 2 * n;
             }
             if (in) {
-                const float avg = T / invB;
+                const float avg = ORD ? T : T / invB;
                 if (MODE == BCH_MODE_RESTART)
                     // T holds the row signs only: sgn(y_u) is common to all its terms
                     y = y + __uint_as_float(__float_as_uint(avg) ^ (y < 0.0f ? 0x80000000u : 0u));
@@ -371,13 +421,16 @@ void launch(const GenericArgs &a, const RowGenTab &t, size_t lds, hipStream_t st
     const dim3 grid((unsigned)a.F), block(NK * WAVE);
     switch (a.mode) {
     case BCH_MODE_RESTART:
-        hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_RESTART>), grid, block, lds, stream, a, t);
+        hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_RESTART, false>), grid, block, lds, stream, a, t);
         break;
     case BCH_MODE_MEMORY:
-        hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_MEMORY>), grid, block, lds, stream, a, t);
+        hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_MEMORY, false>), grid, block, lds, stream, a, t);
         break;
     default:
-        hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_EXTRINSIC>), grid, block, lds, stream, a, t);
+        if (NK == 1 && t.order)
+            hipLaunchKernelGGL((rowgen_decode<1, BCH_MODE_EXTRINSIC, true>), grid, block, lds, stream, a, t);
+        else
+            hipLaunchKernelGGL((rowgen_decode<NK, BCH_MODE_EXTRINSIC, false>), grid, block, lds, stream, a, t);
         break;
     }
 }

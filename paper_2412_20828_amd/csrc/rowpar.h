@@ -58,7 +58,7 @@ struct RowParArgs {
 // Host image of a code's tables; offsets in bytes into `data`.
 struct RowParImage {
     std::vector<uint8_t> data;
-    size_t steps = 0, rounds = 0, mask = 0, slot = 0, recs = 0;
+    size_t steps = 0, rounds = 0, mask = 0, slot = 0, recs = 0, order = 0;
     int n_rounds = 0, n_recs = 0;
     int seg[3] = {0, 0, 0};  // generic kernels: records of a coordinate in shift s (the longest list)
     int sign_words = 0;      // words of a row's message signs
@@ -93,9 +93,11 @@ struct RowGenTab {
     int ns, np;              // shifts and types
     int dp;                  // shift period, 0 for one branch
     int offsets;             // d_o is used (more than one branch)
+    const uint8_t *order;    // [step][kRpCols][64]: position in the order read of a row's columns, ascending (a decoder
+                             // that stands in for a specialised one-branch kernel), or null
 };
 
-bool build_rowgen(const Pcm &p, int n_branches, bool memory, RowParImage &out);
+bool build_rowgen(const Pcm &p, int n_branches, bool memory, bool ordered, RowParImage &out);
 int rowgen_stride(const RowParImage &im, bool memory);
 size_t rowgen_lds_bytes(const RowGenTab &t, int N, int M, int mode);
 
