@@ -46,6 +46,7 @@
 #include <algorithm>
 
 #include "rowpar.h"
+#include "rowsearch.h"
 
 namespace bch {
 namespace {
@@ -53,11 +54,6 @@ namespace {
 constexpr int WAVE = 64;
 constexpr int TYPES = 3;
 constexpr int B = 9;
-
-__device__ __forceinline__ uint32_t med3i(uint32_t a, uint32_t b, uint32_t c)
-{
-    return __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(a), __uint_as_float(b), __uint_as_float(c)));
-}
 
 // ordering of a wave's own LDS traffic: LDS operations of a wave complete in
 // order, so only the compiler has to keep them so
@@ -161,6 +157,41 @@ __device__ __forceinline__ uint2 search_row(const char *Eb, const StepWord *st, 
         if (e < n)
             search_step(Eb, st[e], u1, u2);
     return make_uint2(u1, u2);
+}
+
+template <int NK, bool FIX8>
+__device__ __forceinline__ uint2 row_record(const uint64_t *W, const uint4 &mk, uint2 u);
+
+// a posterior of the frame is NaN: its rows take ordered_row.  Every wave
+// holds the whole frame and finds the same
+template <int NK, bool FIX8>
+__device__ __forceinline__ bool has_nan(const float *y, const bool *in)
+{
+    bool nan = false;
+#pragma unroll
+    for (int j = 0; j < NK; j++)
+        nan = nan || (in[j] && y[j] != y[j]);
+    return !FIX8 && __ballot(nan) != 0ull;
+}
+
+// the two least of a row by its columns mk of the type's input, k at E[k + 2 d_p]
+template <int NK, bool FIX8>
+__device__ __forceinline__ uint2 ordered_row(const uint64_t *W, const float *E, int dp, uint4 mk)
+{
+    // opaque: what depends on the mask alone would be formed ahead of the iterations, and spill
+    __asm__ volatile("" : "+v"(mk.x), "+v"(mk.y), "+v"(mk.z), "+v"(mk.w));
+    uint64_t lo = (uint64_t)mk.y << 32 | mk.x, hi = (uint64_t)mk.w << 32 | mk.z;
+    const uint2 u = ordered_search(__popcll(lo) + (NK == 2 ? __popcll(hi) : 0), [&]() {
+        const bool first = NK == 1 || lo != 0ull;
+        const uint64_t m = first ? lo : hi;
+        lo &= first ? lo - 1ull : ~0ull;
+        hi &= first ? ~0ull : hi - 1ull;
+        return __float_as_uint(E[__builtin_ctzll(m) + (first ? 0 : WAVE) + 2 * dp]);
+    });
+    uint2 r = row_record<NK, FIX8>(W, mk, u);
+    // a row of NaNs: its sign multiplies them there, which leaves theirs
+    r.x &= u.x > 0x7f800000u ? 0x7fffffffu : ~0u;
+    return r;
 }
 
 template <int NK, bool FIX8>
@@ -299,7 +330,12 @@ __device__ __forceinline__ void decode_frame(const RowParArgs &A, const RowParTa
         type_input<NK, FIX8>(E, N, dp, lane, y, in, W, a);
         wave_order();
         // ---- 2. rows
-        {
+        if (has_nan<NK, FIX8>(y, in)) {
+            for (int q = 0; q < tb.n_rounds; q++) {
+                const uint4 mk = tb.mask[q * WAVE + lane];
+                *reinterpret_cast<uint2 *>(Rb + tb.slot[q * WAVE + lane]) = ordered_row<NK, FIX8>(W, E, dp, mk);
+            }
+        } else {
             const StepWord *sp = reinterpret_cast<const StepWord *>(tb.steps);
             StepWord nx = sp[lane];
             for (int q = 0; q < tb.n_rounds; q++) {
@@ -481,10 +517,18 @@ __device__ __forceinline__ void decode_wide(const RowParArgs &A, const RowParTab
         type_input<NK, FIX8>(E, N, dp, lane, y, in, W, a);
         wave_order();
         // ---- 2. rows
-        if (na)
-            *reinterpret_cast<uint2 *>(Rb + slota) = row_record<NK, FIX8>(W, mka, search_row<kRpWideSteps>(Eb, sa, na));
-        if (S2 && nb)
-            *reinterpret_cast<uint2 *>(Rb + slotb) = row_record<NK, FIX8>(W, mkb, search_row<S2>(Eb, sb, nb));
+        if (has_nan<NK, FIX8>(y, in)) {
+            if (na)
+                *reinterpret_cast<uint2 *>(Rb + slota) = ordered_row<NK, FIX8>(W, E, dp, mka);
+            if (S2 && nb)
+                *reinterpret_cast<uint2 *>(Rb + slotb) = ordered_row<NK, FIX8>(W, E, dp, mkb);
+        } else {
+            if (na)
+                *reinterpret_cast<uint2 *>(Rb + slota) =
+                    row_record<NK, FIX8>(W, mka, search_row<kRpWideSteps>(Eb, sa, na));
+            if (S2 && nb)
+                *reinterpret_cast<uint2 *>(Rb + slotb) = row_record<NK, FIX8>(W, mkb, search_row<S2>(Eb, sb, nb));
+        }
         __syncthreads();
         // ---- 3. c2v sums of the coordinates
         float *U = Ubase + (t & 1) * TYPES * US;
