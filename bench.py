@@ -115,25 +115,6 @@ def kernel_src_hash(family):
     return outer.hexdigest()[:16]
 
 
-# kernels with their c2v sums on the matrix cores, which stand in for the
-# registered fixed-point kernel of these matrices in large calls of decoders
-# without a layout flag.  Their algorithmic operations are counted like any
-# kernel's, so their share of the vector peak can pass 1.
-MM_KERNELS = {"spec_bch127_64_m72_b9_fix8", "spec_bch127_99_m33_b9_fix8", "spec_bch63_36_m122_b9_fix8"}
-
-
-def running_kernel(dec, B, F):
-    """Name of the lane-per-frame kernel behind a decode of F frames."""
-    name = dec.kernel_name(F)
-    base = name.replace("_pk16", "").replace("_grp", "")
-    if base in MM_KERNELS and not dec.flags & (B.PACKED16 | B.SMALL_ALWAYS | B.SMALL_NEVER):
-        import torch
-        n_cu = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
-        if F > 92 * n_cu if dec.N > 64 else F >= 2400 * n_cu:
-            return base + "_mm"
-    return name
-
-
 V2C_OPS = {1: 0, 2: 2, 3: 1}  # message mode -> v2c arithmetic per edge (restart, memory, extrinsic)
 
 
@@ -332,7 +313,7 @@ def build_single(args, B, torch, dev, stream, codes, points, precisions, seed_ba
                             dec.decode_into(inp, d_o_d, bits, it, fl, workspace=ws, stream=st))
                 item.inputs, item.outputs = (inp, d_o_d), (bits, it, fl)
                 item.dec, item.ws = dec, ws
-                item.kernel = running_kernel(dec, B, F) if dec.specialized else "generic_%s" % prec
+                item.kernel = dec.running_kernel(F) if dec.specialized else "generic_%s" % prec
 
                 def stats(name=name, prec=prec, code=code, pcm=pcm, bits=bits, it=it, fl=fl, pts=pts):
                     W = bits.cpu().numpy().view(np.uint64)
@@ -398,8 +379,8 @@ def build_mixed(args, B, torch, dev, stream, codes, probs, lohi, precisions, see
         ws = torch.empty(max(1, mix.workspace_size(F)), dtype=torch.uint8, device=dev)
         item = Item("mixed", prec, F, lambda st=stream, mix=mix, inp=inp, bits=bits, it=it, fl=fl, ws=ws:
                     mix.decode_into(ci_d, inp, d_o_d, bits, it, fl, ws, stream=st))
-        # the mixed-code kernel's name, or per-code launches of this precision
-        kname = mix.kernel_name(F)
+        # the kernel's name, or per-code launches of this precision
+        kname = mix.running_kernel(F)
         item.kernel = kname if kname != "per-code" else "per-code_%s" % prec
 
         def stats(prec=prec, bits=bits, it=it, fl=fl):
@@ -591,7 +572,7 @@ def run_latency(args):
                 b.record(stream)
             torch.cuda.synchronize()
             ms = np.array([a.elapsed_time(b) for a, b in ev])
-            rows.append({"code": name, "frames": F, "kernel": dec.kernel_name(F),
+            rows.append({"code": name, "frames": F, "kernel": dec.running_kernel(F),
                          "latency_ms_p50": float(np.percentile(ms, 50)), "latency_ms_p99": float(np.percentile(ms, 99)),
                          "max_iters": int(it.max().item()), "frames_per_s": F / (float(np.median(ms)) / 1e3)})
             print(json.dumps(rows[-1]), file=sys.stderr, flush=True)
@@ -675,7 +656,7 @@ def run_experiment(args):
                              "fer": float((w != truth[:, :w.shape[1]]).any(1).mean()),
                              "avg_iters": float(it.mean()), "frames_per_s": F / sec,
                              "valu_frac": ops / sec / VALU_PEAK_OPS,
-                             "kernel": dec.kernel_name(F) if dec.specialized else "generic"})
+                             "kernel": dec.running_kernel(F) if dec.specialized else "generic"})
         out.update({"workload": "beta", "config": {"workload": "H_o redundancy sweep, 9 branches, restart mode, "
                                                               "%d frames per point" % F}})
     else:
@@ -700,7 +681,7 @@ def run_experiment(args):
                     w, it, fl, sec = timed_decode(dec, llr, d_o, torch, reps=1)
                     ops = float(it.astype(np.int64).sum()) * alg_ops_per_iteration(code.N, code.K, pcm.M, pcm.E,
                                                                                     nb, mode)
-                    rows.append({"code": name, "ebn0": e, "config": label, "kernel": dec.kernel_name(F),
+                    rows.append({"code": name, "ebn0": e, "config": label, "kernel": dec.running_kernel(F),
                                  "fer": float((w != truth[:, :w.shape[1]]).any(1).mean()),
                                  "avg_iters": float(it.mean()), "frames_per_s": F / sec,
                                  "valu_frac": ops / sec / VALU_PEAK_OPS})
@@ -957,6 +938,8 @@ def main():
         for prec in by_prec_kernel:
             if kname in by_prec_kernel[prec]:
                 by_prec_kernel[prec][kname][1:] = [ops_k, n_k]
+    # a kernel with its sums on the matrix cores (..._mm) has its algorithmic
+    # operations counted like any, so its share of the vector peak can pass 1
     roof_prec = {}
     for prec, ks in by_prec_kernel.items():
         kd = max(ks, key=lambda n: ks[n][0])

@@ -204,20 +204,25 @@ int bch_decoder_create(bch_code code, bch_pcm pcm, const bch_dec_params *params,
                        bch_decoder *out);
 /* 1 if the decoder runs a PCM-specialised kernel, 0 for the generic one. */
 int bch_decoder_is_specialized(bch_decoder dec);
-/* Name of the kernel registered for a decode of F frames ("generic" for the
- * generic kernel, "" for a null decoder); the string is static and owned by
- * the library.  Nine-branch restart-mode decoders without BCH_DEC_PACKED16,
- * BCH_DEC_SMALL_ALWAYS or BCH_DEC_SMALL_NEVER run small calls (N = 127: up to
- * 92 frames per CU, N = 63: 224, a mixed-code call without either of its
- * flags: 256) on the row-parallel kernel instead, a frame per workgroup in one
- * launch, with the same results bit for bit; the name is that of the
- * lane-per-frame kernel it stands in for.  So it is with the fixed-point kernel
- * whose sums run on the matrix cores, in decoders without those three flags:
- * (127,64) with 72 and (127,99) with 33 rows from 92 frames per CU on (the
- * row-parallel kernel's limit), (63,36) with 122 rows from 2400.
- * Specialised one-branch decoders without the two SMALL flags run calls of up
- * to 64 frames per CU on the generic kernel's frame-per-workgroup form. */
+/* Name of the lane-per-frame kernel registered for a decode of F frames
+ * ("generic" without one, "" for a null decoder); the string is static and
+ * owned by the library.  Others stand in for it where they are faster, with the
+ * same results bit for bit: bch_decoder_running_kernel. */
 const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F);
+/* Name of the kernel that bch_nms_decode_batch runs on F frames ("" for a null
+ * decoder); static, owned by the library.  The name registered, or
+ *   "rowpar", "rowpar_wide"  a frame per workgroup in one launch (wide: four
+ *       waves a type, up to a frame per CU): small calls of nine-branch
+ *       restart-mode decoders without BCH_DEC_PACKED16, BCH_DEC_SMALL_ALWAYS or
+ *       BCH_DEC_SMALL_NEVER
+ *   "spec_..._mm"  sums on the matrix cores: larger fixed-point calls of
+ *       (127,64) with 72, (127,99) with 33 and, from 2400 frames per CU, (63,36)
+ *       with 122 rows, in decoders without those three flags
+ *   "rowgen"   a frame per workgroup, any matrix: every generic decode whose
+ *       state fits, and calls of up to 64 frames per CU of specialised
+ *       one-branch extrinsic decoders without the two SMALL flags
+ *   "generic"  a frame per lane, any matrix. */
+const char *bch_decoder_running_kernel(bch_decoder dec, int64_t F);
 void bch_decoder_destroy(bch_decoder dec);
 
 /* Device workspace (bytes) a decode of F frames needs (0 for some configs). */
@@ -300,9 +305,11 @@ int bch_mixed_decode_batch(const bch_decoder *decs, int n_codes, const uint8_t *
 
 /* Name of the kernel registered for a mixed call of F frames over
  * decs[0..n_codes): the mixed-code kernel's, or "per-code" ("" for bad
- * arguments); static, owned by the library.  Small calls run the row-parallel
- * kernel in its place (bch_decoder_kernel_name). */
+ * arguments); static, owned by the library. */
 const char *bch_mixed_kernel_name(const bch_decoder *decs, int n_codes, int64_t F);
+/* Name of the kernel that bch_mixed_decode_batch runs on F frames: that name, or
+ * "rowpar", "rowpar_wide" for small calls (bch_decoder_running_kernel). */
+const char *bch_mixed_running_kernel(const bch_decoder *decs, int n_codes, int64_t F);
 
 /* Syndrome test of eq. 5 with the code's standard PCM: ok[f] = 1 iff
  * H c_f^T = 0.  bits: device [F][ceil(N/64)] uint64; ok: device [F] uint8. */

@@ -39,6 +39,7 @@ SYMBOLS = [
     "bch_syndrome_check", "bch_quantize_llr", "bch_osd_decode", "bch_decoder_set_tuning",
     "bch_mixed_workspace_size", "bch_mixed_decode_batch", "bch_osd_decode_device", "bch_mixed_osd_decode",
     "bch_draw_offsets", "bch_draw_offsets_keys", "bch_pcm_stats", "bch_nms_decode_batch_noalloc", "bch_mixed_kernel_name",
+    "bch_decoder_running_kernel", "bch_mixed_running_kernel",
 ]
 MAX_MIX = 8
 
@@ -94,6 +95,8 @@ def lib():
     L.bch_decoder_is_specialized.argtypes = [P]
     L.bch_decoder_kernel_name.argtypes = [P, ctypes.c_int64]
     L.bch_decoder_kernel_name.restype = ctypes.c_char_p
+    L.bch_decoder_running_kernel.argtypes = [P, ctypes.c_int64]
+    L.bch_decoder_running_kernel.restype = ctypes.c_char_p
     L.bch_decoder_destroy.argtypes = [P]
     L.bch_decoder_destroy.restype = None
     L.bch_decode_workspace_size.argtypes = [P, i64]
@@ -109,6 +112,8 @@ def lib():
     L.bch_mixed_decode_batch.argtypes = [P, i32, P, P, i64, i64, P, P, i64, P, P, P, ctypes.c_size_t, P]
     L.bch_mixed_kernel_name.argtypes = [P, i32, ctypes.c_int64]
     L.bch_mixed_kernel_name.restype = ctypes.c_char_p
+    L.bch_mixed_running_kernel.argtypes = [P, i32, ctypes.c_int64]
+    L.bch_mixed_running_kernel.restype = ctypes.c_char_p
     L.bch_osd_decode_device.argtypes = [P, P, i64, i64, i32, P, P, i64, P]
     L.bch_mixed_osd_decode.argtypes = [P, i32, P, P, i64, i64, i32, P, P, i64, P]
     _lib = L
@@ -270,8 +275,13 @@ class Decoder:
         return bool(lib().bch_decoder_is_specialized(self.h))
 
     def kernel_name(self, F):
-        """Name of the kernel a decode of F frames runs."""
+        """Name of the lane-per-frame kernel registered for a decode of F frames."""
         return lib().bch_decoder_kernel_name(self.h, F).decode()
+
+    def running_kernel(self, F):
+        """Name of the kernel a decode of F frames runs: the one registered, or
+        the one that stands in for it (bch_decoder_running_kernel)."""
+        return lib().bch_decoder_running_kernel(self.h, F).decode()
 
     def set_tuning(self, waves_per_cu: int = 0):
         """Waves per CU of the persistent grid (0: the kernel's default)."""
@@ -334,10 +344,10 @@ class Decoder:
 
 
 class MixedDecoder:
-    """Frames of several codes interleaved in one batch: one code-keyed
-    prepass and one persistent kernel when the library has a mixed-code
-    kernel for these matrices, else one of each per code, all enqueued on one
-    stream."""
+    """Frames of several codes interleaved in one batch, all enqueued on one
+    stream: a small call is one launch of the row-parallel kernel; a larger one
+    one code-keyed prepass and one persistent kernel when the library has a
+    mixed-code kernel for these matrices, else one of each per code."""
 
     def __init__(self, decoders):
         if not 1 <= len(decoders) <= MAX_MIX:
@@ -351,8 +361,13 @@ class MixedDecoder:
         return int(lib().bch_mixed_workspace_size(self._arr, len(self.decoders), F))
 
     def kernel_name(self, F: int) -> str:
-        """The mixed-code kernel a call of F frames runs, or "per-code"."""
+        """The mixed-code kernel registered for a call of F frames, or "per-code"."""
         return lib().bch_mixed_kernel_name(self._arr, len(self.decoders), F).decode()
+
+    def running_kernel(self, F: int) -> str:
+        """Name of the kernel a call of F frames runs: kernel_name's, or the
+        row-parallel kernel in its place (bch_mixed_running_kernel)."""
+        return lib().bch_mixed_running_kernel(self._arr, len(self.decoders), F).decode()
 
     def decode_into(self, code_idx, llr, d_o, bits, iters, flags, workspace, stream=None):
         F, ld = llr.shape

@@ -242,23 +242,11 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
 static int64_t rowpar_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * (d->N > 64 ? 92 : 224); }
 static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
 
-// one launch of the row-parallel kernel: frame f with decs[code_idx[f]] (or
-// decs[0] without a code index)
-static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *code_idx, const void *llr, int64_t ld,
-                         int64_t F, const uint8_t *d_o, uint64_t *bits, int64_t bits_ld, uint8_t *iters,
-                         uint8_t *flags, void *trace, hipStream_t stream)
+// codes and shape of a row-parallel call of F frames
+static RowParArgs rowpar_args(const bch_decoder *decs, int n_codes, int64_t F)
 {
     RowParArgs a{};
-    a.llr = llr;
-    a.ld = ld;
     a.F = F;
-    a.d_o = d_o;
-    a.code_idx = code_idx;
-    a.bits = bits;
-    a.bits_ld = bits_ld;
-    a.iters = iters;
-    a.flags = flags;
-    a.trace = trace;
     a.n_codes = n_codes;
     // up to a workgroup a CU, where a frame's own time counts: four waves a type
     // instead of one.  One frame (eight iterations) and 256, us: (127,64) 37.5
@@ -269,8 +257,32 @@ static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *co
     a.wide = F <= decs[0]->n_cu;
     for (int c = 0; c < n_codes; c++)
         a.tab[c] = decs[c]->rowpar;
+    return a;
+}
+
+// one launch of the row-parallel kernel: frame f with decs[code_idx[f]] (or
+// decs[0] without a code index)
+static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *code_idx, const void *llr, int64_t ld,
+                         int64_t F, const uint8_t *d_o, uint64_t *bits, int64_t bits_ld, uint8_t *iters,
+                         uint8_t *flags, void *trace, hipStream_t stream)
+{
+    RowParArgs a = rowpar_args(decs, n_codes, F);
+    a.llr = llr;
+    a.ld = ld;
+    a.d_o = d_o;
+    a.code_idx = code_idx;
+    a.bits = bits;
+    a.bits_ld = bits_ld;
+    a.iters = iters;
+    a.flags = flags;
+    a.trace = trace;
     hipError_t e = launch_rowpar(a, decs[0]->prm.precision == BCH_FIX8, stream);
     return e == hipSuccess ? BCH_OK : hip_fail(e, "row-parallel kernel launch");
+}
+
+static const char *rowpar_name(const bch_decoder *decs, int n_codes, int64_t F)
+{
+    return rowpar_is_wide(rowpar_args(decs, n_codes, F)) ? "rowpar_wide" : "rowpar";
 }
 
 // Largest call of the generic frame-per-workgroup kernel (k_rowgen.hip) in the
@@ -283,6 +295,30 @@ static int rowpar_decode(const bch_decoder *decs, int n_codes, const uint8_t *co
 //            20000: 220 / 112, 196 / 194
 // hence 64 frames per CU
 static int64_t rowgen_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * 64; }
+
+// the kernel of a decode of F frames, of a decoder's own calls
+enum class Route { kRowPar, kRowGen, kSpec, kGeneric };
+
+static Route route_of(const bch_decoder_s *d, int64_t F)
+{
+    if (d->d_rowpar && F <= rowpar_max_frames(d))
+        return Route::kRowPar;
+    // a generic decoder: wherever its tables and state fit (24-400 times the
+    // one-lane-per-frame kernel's rate, k_rowgen.hip), whatever the call's size
+    if (d->d_rowgen && (!d->spec || F <= rowgen_max_frames(d)))
+        return Route::kRowGen;
+    return d->spec ? Route::kSpec : Route::kGeneric;
+}
+
+// a mixed call runs the row-parallel kernel in one launch
+static bool mixed_rowpar(const bch_decoder *decs, int n_codes, int64_t F)
+{
+    for (int c = 0; c < n_codes; c++)
+        if (!decs[c]->d_rowpar || F > rowpar_max_mixed(decs[c]) ||
+            (decs[c]->prm.flags & (BCH_DEC_NO_MIXED_KERNEL | BCH_DEC_MIXED_KERNEL)))
+            return false;
+    return true;
+}
 
 // device copy of a decoder's row-parallel tables
 static hipError_t make_rowpar(bch_decoder_s *d, const Pcm &p)
@@ -815,6 +851,18 @@ const char *bch_decoder_kernel_name(bch_decoder dec, int64_t F)
     return dec->spec ? spec_for(dec, F)->name : "generic";
 }
 
+const char *bch_decoder_running_kernel(bch_decoder dec, int64_t F)
+{
+    if (!dec)
+        return "";
+    switch (route_of(dec, F)) {
+    case Route::kRowPar: return rowpar_name(&dec, 1, F);
+    case Route::kRowGen: return "rowgen";
+    case Route::kSpec: return spec_run(dec, F)->name;
+    default: return "generic";
+    }
+}
+
 void bch_decoder_destroy(bch_decoder dec)
 {
     if (!dec)
@@ -874,9 +922,10 @@ int bch_nms_decode_batch(bch_decoder dec, const void *llr, int64_t ld, int64_t F
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess || cur != dec->dev)
         return fail(BCH_EINVAL, "decoder belongs to another device");
-    if (dec->d_rowpar && F <= rowpar_max_frames(dec))
+    const Route route = route_of(dec, F);
+    if (route == Route::kRowPar)
         return rowpar_decode(&dec, 1, nullptr, llr, ld, F, d_o, bits, dec->W64, iters, flags, y_trace, stream);
-    if (dec->spec && !(dec->d_rowgen && F <= rowgen_max_frames(dec)))
+    if (route == Route::kSpec)
         return spec_decode(dec, llr, ld, F, d_o, nullptr, 0, bits, dec->W64, iters, flags, y_trace, workspace,
                            stream);
     GenericArgs a{};
@@ -905,9 +954,7 @@ int bch_nms_decode_batch(bch_decoder dec, const void *llr, int64_t ld, int64_t F
     float *ws = static_cast<float *>(workspace);
     a.ws_c2v = ws;
     a.ws_s = ws ? ws + (size_t)a.B * a.E * F : nullptr;
-    // the frame-per-workgroup kernel wherever its tables and state fit (24-400
-    // times the other's rate, k_rowgen.hip), whatever the call's size
-    hipError_t e = dec->d_rowgen ? launch_rowgen(a, dec->rowgen, stream) : launch_generic_fp32(a, stream);
+    hipError_t e = route == Route::kRowGen ? launch_rowgen(a, dec->rowgen, stream) : launch_generic_fp32(a, stream);
     return e == hipSuccess ? BCH_OK : hip_fail(e, "generic kernel launch");
 }
 
@@ -989,11 +1036,7 @@ int bch_mixed_decode_batch(const bch_decoder *decs, int n_codes, const uint8_t *
     const size_t need = bch_mixed_workspace_size(decs, n_codes, F);
     if (!workspace || ws_bytes < need)
         return fail(BCH_ENOMEM, "workspace too small");
-    bool rowpar = true;
-    for (int c = 0; c < n_codes; c++)
-        rowpar = rowpar && decs[c]->d_rowpar && F <= rowpar_max_mixed(decs[c]) &&
-                 !(decs[c]->prm.flags & (BCH_DEC_NO_MIXED_KERNEL | BCH_DEC_MIXED_KERNEL));
-    if (rowpar)
+    if (mixed_rowpar(decs, n_codes, F))
         return rowpar_decode(decs, n_codes, code_idx, llr, ld, F, d_o, bits, bits_ld, iters, flags, nullptr, stream);
     if (const bch::MixKernel *k = mixed_kernel_of(decs, n_codes, F))
         return mixed_fused(k, decs, n_codes, code_idx, llr, ld, F, d_o, bits, bits_ld, iters, flags, workspace,
@@ -1015,6 +1058,18 @@ const char *bch_mixed_kernel_name(const bch_decoder *decs, int n_codes, int64_t 
         return "";
     const bch::MixKernel *k = mixed_kernel_of(decs, n_codes, F);
     return k ? k->name : "per-code";
+}
+
+const char *bch_mixed_running_kernel(const bch_decoder *decs, int n_codes, int64_t F)
+{
+    if (!decs || n_codes < 1 || n_codes > BCH_MAX_MIX || F < 0)
+        return "";
+    for (int c = 0; c < n_codes; c++)
+        if (!decs[c])
+            return "";
+    if (mixed_rowpar(decs, n_codes, F))
+        return rowpar_name(decs, n_codes, F);
+    return bch_mixed_kernel_name(decs, n_codes, F);
 }
 
 int bch_osd_decode_device(bch_decoder dec, const float *llr, int64_t ld, int64_t F, int order,

@@ -612,27 +612,35 @@ void launch(const RowParArgs &a, int len, size_t lds, hipStream_t stream)
 
 }  // namespace
 
+bool rowpar_is_wide(const RowParArgs &a)
+{
+    bool wide = a.wide != 0;
+    for (int c = 0; c < a.n_codes; c++) {
+        const RowParTab &t = a.tab[c];
+        wide = wide && t.wide && rowpar_lds_bytes(t.N, t.M, t.dp, kRpWide) <= kRpMaxLds;
+    }
+    return wide;
+}
+
 hipError_t launch_rowpar(const RowParArgs &a, int fix8, hipStream_t stream)
 {
     if (a.F < 1 || a.n_codes < 1 || a.n_codes > kRpMaxCodes || a.F > (int64_t)0x7fffffff)
         return hipErrorInvalidValue;
-    size_t lds = 0, lds_wide = 0;
-    bool one = false, two = false, wide = a.wide != 0;
+    const bool wide = rowpar_is_wide(a);
+    size_t lds = 0;
+    bool one = false, two = false;
     for (int c = 0; c < a.n_codes; c++) {
         const RowParTab &t = a.tab[c];
-        lds = std::max(lds, rowpar_lds_bytes(t.N, t.M, t.dp, 1));
-        lds_wide = std::max(lds_wide, rowpar_lds_bytes(t.N, t.M, t.dp, kRpWide));
-        wide = wide && t.wide;
+        lds = std::max(lds, rowpar_lds_bytes(t.N, t.M, t.dp, wide ? kRpWide : 1));
         (t.N > WAVE ? two : one) = true;
     }
     if (lds > kRpMaxLds)
         return hipErrorInvalidValue;
-    wide = wide && lds_wide <= kRpMaxLds;
     const int len = one && two ? 0 : (two ? 2 : 1);
     if (wide && fix8)
-        launch<true, kRpWide>(a, len, lds_wide, stream);
+        launch<true, kRpWide>(a, len, lds, stream);
     else if (wide)
-        launch<false, kRpWide>(a, len, lds_wide, stream);
+        launch<false, kRpWide>(a, len, lds, stream);
     else if (fix8)
         launch<true, 1>(a, len, lds, stream);
     else

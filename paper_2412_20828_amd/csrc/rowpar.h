@@ -105,5 +105,7 @@ struct GenericArgs;
 hipError_t launch_rowgen(const GenericArgs &a, const RowGenTab &t, hipStream_t stream);
 
 hipError_t launch_rowpar(const RowParArgs &a, int fix8, hipStream_t stream);
+// launch_rowpar runs kRpWide waves a type on these codes
+bool rowpar_is_wide(const RowParArgs &a);
 
 }  // namespace bch
