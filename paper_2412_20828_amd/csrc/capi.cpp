@@ -217,29 +217,25 @@ static int spec_decode(const bch_decoder_s *d, const void *llr, int64_t ld, int6
     return e == hipSuccess ? BCH_OK : hip_fail(e, "specialised kernel launch");
 }
 
-// Largest call of the row-parallel kernel (k_rowpar.hip), whose time grows with
-// the frame-iterations from the first frame on; the lane-per-frame kernels
-// take the time of their slowest frame's iterations up to about 64 frames per
-// CU and stop early only frame by frame.  Measured in us per call, row-parallel
-// against the kernel that takes the call otherwise, at 2 / 3 / 5 dB (2 dB the
-// hardest case, 3.0-7.6 iterations a frame), on 256 CUs:
-//   N = 127, 72 rows  16384: 676 / 545 / -, 888 / 618 / -
-//                     24576: 949 / 771 / 241, 918 / 912 / 574
-//                     28672: 1086 / 875 / 279, 925 / 922 / 583
-//   N = 127, 33 rows  24576: 788 / 610 / 171, 809 / 800 / 467
-//                     28672: 907 / 720 / 203, 814 / 808 / 507
-//   N = 63, 122 rows  49152: 900 / 503 / -, 1017 / 997 / -
-//                     57344: 996 / 581 / 304, 1007 / 1008 / 621
-//   N = 63, 33 rows   49152: 279 / 176 / -, 330 / 325 / -
-//                     57344: 321 / 197 / 120, 338 / 335 / 210
-// hence 92 frames per CU for N > 64 and 224 for N <= 64, where no Eb/N0 loses.
-// Fixed point, N = 127, 72 rows, against the kernel with its sums on the matrix
-// cores (about 690 at any of these sizes and Eb/N0):
-//   20480: 862 / 704 / 235   24576: 993 / 830 / 268
+// Largest call of the row-parallel kernel (k_rowpar.hip): the line measured for
+// the registered kernel (gen_spec.ROWPAR_FRAMES), eight iterations at most.  Of
+// fewer a frame runs the greater part, so that the lane-per-frame kernels catch
+// up earlier, for N <= 64 at about 7 / 7, 5 / 7, 3 / 7 and a quarter of the line
+// with 8, 6, 4 and 2.  (63,36) with 122 rows, (63,45) with 33, at 2 dB, us,
+// row-parallel / lane-per-frame, frames per CU:
+//   6   168: 647/669  196: 751/778    168: 223/227  196: 257/255
+//   4    96: 317/303  112: 361/308     84: 103/117  112: 133/121
+//   2    56: 136/131   84: 191/164     56: 54/62     84: 73/74
+// For N > 64 the line stays (72 rows, 92: 455/486 with 4, 238/252 with 2).
+static int64_t rowpar_max_frames(const bch_decoder_s *d)
+{
+    const int64_t most = (int64_t)d->n_cu * d->spec->rowpar_frames;
+    return d->N > 64 ? most : most * std::min(std::max(4 * (d->prm.max_iter - 1), 7), 28) / 28;
+}
+
 // A mixed-code call of the service's four codes takes 899 / 1450 us at 32768
 // frames, 1684 / 1731 at 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455
 // at 65536 over 2-5 dB): 256 per CU.
-static int64_t rowpar_max_frames(const bch_decoder_s *d) { return (int64_t)d->n_cu * (d->N > 64 ? 92 : 224); }
 static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
 
 // codes and shape of a row-parallel call of F frames

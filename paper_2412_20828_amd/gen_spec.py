@@ -67,6 +67,44 @@ SPECS = [
     ("bch63_36", 0, 1, 3, 0, 8),
     ("bch63_45", 0, 1, 3, 0, 8),
 ]
+# nine-branch restart-mode kernels: largest call, in frames per CU, that the
+# row-parallel kernel (k_rowpar.hip) takes in their place.  Its time grows with
+# the frame-iterations from the first frame on; the lane-per-frame kernels take
+# the time of their slowest frame's iterations, in steps of about 64 frames per
+# CU, and stop early only frame by frame.  So it is the faster the fewer
+# iterations a frame runs: the hardest of 2-5 dB is 2 dB.  Measured, us a call,
+# eight iterations at most, 256 CUs, row-parallel / lane-per-frame at so many
+# frames per CU.  FP32: at the line at 2 / 3 / 5 dB, then past it at 2 dB.
+#   N = 127, 72 rows   92: 857/921   710/913   235/528     100: 931/923
+#            65        92: 953/1262  715/1258  215/1247
+#            57        92: 762/878   570/710   175/497     100: 820/871
+#            49        92: 737/980   572/983   175/972
+#            33        92: 716/810   568/762   168/464     100: 772/811
+#   (63,45), 33 rows  224: 314/337   202/335   120/201
+#   (63,36), 122      224: 994/1024  584/1015  312/632     256: 1119/1035
+#            27        76: 165/175   112/174    57/167      96: 208/178
+#            32        88: 192/194   128/195    65/182     112: 238/198
+#            47        96: 265/258   170/257    87/229     112: 305/262
+#           269       208: 2022/2103 1187/2106 683/1270    224: 2144/2098
+#           316       188: 2302/2444 1357/2456 774/1459    208: 2491/2447
+# (just under a step of the other kernel's time, at 112-123 and 176-187, the last
+# two lose up to 11% at 2 dB and win by a third at 3 dB).  Fixed point, N = 63:
+# 122 rows 208: 1031/1051 610/1052 327/622, 33 rows 224: 341/366 222/363 129/229.
+# Fixed point, N = 127, against the kernel with its sums on the matrix cores,
+# whose time hardly depends on Eb/N0, at 2 / 3 / 4 / 5 dB:
+#   72 rows   64: 709/662  593/664  372/667  200/666
+#             92: 970/668  805/669  500/671  270/671     110: 1159/667 963/670 589/673 314/675
+#   33 rows   64: 593/472  479/473  279/474  149/474
+#             84: 742/473  609/476  347/477  183/476      92:  813/474 664/478 376/478 194/479
+# From 60 (72 rows) and 50 (33) frames per CU on it loses at 2 dB, up to 110 and
+# more it wins at 5 dB: the line lies where the four times together cross, below
+# 95 and 84.
+ROWPAR_FRAMES = {  # (code name, rows): FP32, fixed point
+    ("bch63_45", 33): (224, 224), ("bch63_36", 122): (224, 208), ("bch127_64", 72): (92, 92),
+    ("bch127_99", 33): (92, 84), ("bch127_78", 57): (92, 0), ("bch127_78", 49): (92, 0), ("bch127_78", 65): (92, 0),
+    ("bch63_36", 27): (76, 0), ("bch63_36", 32): (88, 0), ("bch63_36", 47): (100, 0), ("bch63_36", 269): (208, 0),
+    ("bch63_36", 316): (188, 0),
+}
 # mixed-code kernels: one persistent launch over frames of these codes, code k
 # of a mixed call being the k-th matrix here: the mixed workload's codes (FP32
 # and fixed point) and the serving engine's four codes (FP32)
@@ -906,11 +944,12 @@ def generate(stage1_lib: str, out_dir: str):
                                            "nms_spec_pk16.inc" if pk16 else "nms_spec_group.inc" if group else "nms_spec_fp32.inc"))
         srcs.append(src_path)
         decls.append("namespace %s { hipError_t launch(const SpecLaunch &, int, int, hipStream_t); }" % ns)
-        entries.append("    {0x%016xull, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, \"%s\", &%s::launch}," %
+        rowpar = ROWPAR_FRAMES[(name, rows)][prec] if B == 9 and mode == 1 else 0
+        entries.append("    {0x%016xull, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, \"%s\", &%s::launch, %d}," %
                        (fingerprint(H), N, M, B, mode, prec, variant, waves, 1 if N > 64 and not regacc else 0,
-                        128 if pk16 else 64, 3 if group else 1, ns, ns))
+                        128 if pk16 else 64, 3 if group else 1, ns, ns, rowpar))
     table = "\n".join(decls) + "\nstatic const SpecKernel kSpecKernels[] = {\n" + "\n".join(entries) + \
-        "\n    {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, nullptr, nullptr}};\n"
+        "\n    {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, nullptr, nullptr, 0}};\n"
     mdecls, mentries = [], []
     for codes, prec in MIXES:
         parts = []

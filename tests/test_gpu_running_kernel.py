@@ -77,3 +77,37 @@ def test_mixed(B):
     for f, want in ((B.MIXED_KERNEL, fused), (B.NO_MIXED_KERNEL, "per-code")):
         m = B.MixedDecoder([make(B, n, flags=f) for n in names])
         assert m.running_kernel(1) == m.kernel_name(1) == want
+
+
+@pytest.mark.parametrize("name,rows,prec,per_cu", [
+    ("bch127_64", 72, 0, 92), ("bch127_78", 57, 0, 92), ("bch127_99", 33, 0, 92), ("bch127_64", 72, 1, 92),
+    ("bch127_99", 33, 1, 84), ("bch63_45", 33, 0, 224), ("bch63_36", 122, 0, 224), ("bch63_36", 122, 1, 208),
+    ("bch63_36", 27, 0, 76), ("bch63_36", 32, 0, 88), ("bch63_36", 47, 0, 100), ("bch63_36", 269, 0, 208),
+    ("bch63_36", 316, 0, 188)])
+def test_both_sides_of_the_row_parallel_line(B, name, rows, prec, per_cu):
+    """The kernels on either side, and that they give the same frames."""
+    F = per_cu * cus()
+    dec = make(B, name, rows, precision=prec)
+    assert dec.running_kernel(F) == "rowpar" and dec.running_kernel(F + 1).startswith("spec_%s_m%d" % (name, rows))
+    N = dec.N
+    g = torch.Generator(device="cuda")
+    g.manual_seed(per_cu)
+    llr = 2.0 + 2.5 * torch.randn((F + 1, 64 if N <= 64 else 128), generator=g, device="cuda")
+    if prec:
+        llr = torch.clamp(torch.round(4.0 * llr), -127, 127).to(torch.int8)
+    d_o = torch.randint(0, B.shift_period(N), (F + 1,), generator=g, device="cuda").to(torch.uint8)
+    a = dec.decode(llr[:F].contiguous(), d_o[:F].contiguous())
+    b = dec.decode(llr, d_o)
+    torch.cuda.synchronize()
+    for x, y in zip(a[:3], b[:3]):
+        assert torch.equal(x, y[:F])
+
+
+def test_line_of_fewer_iterations(B):
+    """The short codes leave the row-parallel kernel earlier, the long ones do not."""
+    for it, per_cu in ((1, 56), (2, 56), (4, 96), (6, 160), (8, 224), (20, 224)):
+        dec = make(B, "bch63_36", max_iter=it)
+        assert dec.running_kernel(per_cu * cus()) == "rowpar"
+        assert dec.running_kernel(per_cu * cus() + 1) == "spec_bch63_36_m122_b9"
+        dec = make(B, "bch127_64", max_iter=it)
+        assert dec.running_kernel(92 * cus()) == "rowpar"
