@@ -159,14 +159,15 @@ enum {
                                   matrices of N = 63 and 127.  Without this flag a fixed-point
                                   decode of at least 4,000,000 frames (N = 127) or 8,000,000
                                   (N = 63) runs it where registered and where the kernel with
-                                  its sums on the matrix cores (bch_decoder_kernel_name) does
+                                  its sums on the matrix cores (bch_decoder_running_kernel) does
                                   not stand in for it, a smaller one the kernel that holds its
                                   integers in 32-bit registers */
     BCH_DEC_SMALL_ALWAYS = 4,  /* N = 127: always use the small-batch kernel (the nine
                                   branches of 64 frames on three waves) where registered */
     BCH_DEC_SMALL_NEVER = 8,   /* N = 127: never use it.  Without either flag a decode of at
-                                  most 92 frames per CU runs the row-parallel kernel, FP32
-                                  ones of up to 128 per CU this one, a larger one the kernel
+                                  most 92 frames per CU (fixed point, (127,99): 84) runs the
+                                  row-parallel kernel, FP32 ones of up to 128 per CU this
+                                  one, a larger one the kernel
                                   of one wave per 64 frames; either
                                   flag also excludes the row-parallel kernel and the one with
                                   its sums on the matrix cores (both code lengths); the
@@ -288,10 +289,11 @@ int bch_decoder_set_tuning(bch_decoder dec, int waves_per_cu);
  * over: one launch saves the per-code launch tails, which dominate small
  * batches, while at large batches each code's own kernel is faster (the
  * 63-bit codes' kernels run three waves per SIMD, the mixed kernel one, and
- * large fixed-point calls take kernels of their own).  Calls of at most
- * 256 frames per CU run the row-parallel kernel (bch_decoder_kernel_name) in
- * one launch of any codes, unless a decoder has one of those two flags or
- * excludes it.  No host synchronisation, no memset: the call
+ * large fixed-point calls take kernels of their own).  Small calls
+ * run the row-parallel kernel (bch_mixed_running_kernel) in one launch of any
+ * codes, unless a decoder has one of those two flags or excludes it: of one
+ * code up to the size of its own calls, else up to 192 frames per CU (most
+ * codes long) or 256.  No host synchronisation, no memset: the call
  * can be captured in a HIP graph and replayed.  Per-frame results do not
  * depend on the mix or the path: each frame decodes exactly as alone.
  */

@@ -233,11 +233,6 @@ static int64_t rowpar_max_frames(const bch_decoder_s *d)
     return d->N > 64 ? most : most * std::min(std::max(4 * (d->prm.max_iter - 1), 7), 28) / 28;
 }
 
-// A mixed-code call of the service's four codes takes 899 / 1450 us at 32768
-// frames, 1684 / 1731 at 65536 and 3153 / 2907 at 131072 at 2 dB (1038 / 1455
-// at 65536 over 2-5 dB): 256 per CU.
-static int64_t rowpar_max_mixed(const bch_decoder_s *d) { return (int64_t)d->n_cu * 256; }
-
 // codes and shape of a row-parallel call of F frames
 static RowParArgs rowpar_args(const bch_decoder *decs, int n_codes, int64_t F)
 {
@@ -304,16 +299,6 @@ static Route route_of(const bch_decoder_s *d, int64_t F)
     if (d->d_rowgen && (!d->spec || F <= rowgen_max_frames(d)))
         return Route::kRowGen;
     return d->spec ? Route::kSpec : Route::kGeneric;
-}
-
-// a mixed call runs the row-parallel kernel in one launch
-static bool mixed_rowpar(const bch_decoder *decs, int n_codes, int64_t F)
-{
-    for (int c = 0; c < n_codes; c++)
-        if (!decs[c]->d_rowpar || F > rowpar_max_mixed(decs[c]) ||
-            (decs[c]->prm.flags & (BCH_DEC_NO_MIXED_KERNEL | BCH_DEC_MIXED_KERNEL)))
-            return false;
-    return true;
 }
 
 // device copy of a decoder's row-parallel tables
@@ -409,6 +394,34 @@ static const bch::MixKernel *mixed_kernel_of(const bch_decoder *decs, int n, int
     if (!forced && F >= BCH_MIXED_KERNEL_MAX_FRAMES)
         return nullptr;
     return find_mix_kernel(fps, n, decs[0]->prm.precision);
+}
+
+// A mixed call runs the row-parallel kernel in one launch: of one code up to the
+// line of its own calls, else up to 256 frames per CU, or 192 where most of the
+// codes are long and the calls otherwise take the mixed-code or the matrix-core
+// kernels.  us, row-parallel / otherwise, frames per CU, at 2 / 3 / 5 dB:
+//   the service's four, FP32  128: 842/1452 633/1431 234/1395  256: 1596/1711 1172/1530 435/1418
+//     fixed point             256: 1803/2522 1358/2526 466/1903
+//   (127,64) (127,99) (63,36) 192: 1463/1464 1079/1466 368/1422
+//                             224: 1701/1466 1256/1460 426/1420  256: 2009/2449 1456/1681 491/1417
+//     fixed point             192: 1560/1509 1197/1514 404/1469  224: 1804/1500 1371/1504 465/1478
+//   (127,64) (127,99), FP32   108: 947/938 759/931 235/893
+//                             144: 1404/2229 1102/2219 320/2182  256: 2398/2262 1906/2283 536/2240
+//     fixed point             192: 1880/1180 1530/1189 446/1184 (3 dB and 4 dB: 893/1189)
+//   (63,36) (63,45), FP32     256: 804/1367 484/1350 276/740
+// Two long codes in FP32 lose up to 9% at 2 dB at 100-122, and win by 10% at 3 dB.
+static bool mixed_rowpar(const bch_decoder *decs, int n_codes, int64_t F)
+{
+    int n_long = 0;
+    for (int c = 0; c < n_codes; c++) {
+        if (!decs[c]->d_rowpar || (decs[c]->prm.flags & (BCH_DEC_NO_MIXED_KERNEL | BCH_DEC_MIXED_KERNEL)))
+            return false;
+        n_long += decs[c]->N > 64;
+    }
+    if (n_codes == 1)
+        return F <= rowpar_max_frames(decs[0]);
+    const bool fast = decs[0]->prm.precision == BCH_FIX8 || mixed_kernel_of(decs, n_codes, F);
+    return F <= (int64_t)decs[0]->n_cu * (2 * n_long > n_codes && fast ? 192 : 256);
 }
 
 // one code-keyed prepass and one persistent kernel over every frame of the mix

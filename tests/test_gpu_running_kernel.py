@@ -111,3 +111,29 @@ def test_line_of_fewer_iterations(B):
         assert dec.running_kernel(per_cu * cus() + 1) == "spec_bch63_36_m122_b9"
         dec = make(B, "bch127_64", max_iter=it)
         assert dec.running_kernel(92 * cus()) == "rowpar"
+
+
+@pytest.mark.parametrize("names,prec,per_cu,past", [
+    (["bch127_64"], 0, 92, "per-code"), (["bch127_99"], 1, 84, "per-code"), (["bch63_36"], 0, 224, "per-code"),
+    (["bch127_64", "bch127_99", "bch63_36"], 0, 192, "mix_127_64_m72_127_99_m33_63_36_m122"),
+    (["bch127_64", "bch127_99", "bch63_36"], 1, 192, "mix_127_64_m72_127_99_m33_63_36_m122_fix8"),
+    (["bch127_64", "bch127_99"], 0, 256, "per-code"), (["bch127_64", "bch127_99"], 1, 192, "per-code"),
+    (["bch63_36", "bch63_45"], 0, 256, "per-code"),
+    (["bch63_36", "bch63_45", "bch127_64", "bch127_99"], 0, 256, "mix_63_36_m122_63_45_m33_127_64_m72_127_99_m33"),
+    (["bch63_36", "bch63_45", "bch127_64", "bch127_99"], 1, 256, "per-code")])
+def test_both_sides_of_the_mixed_line(B, names, prec, per_cu, past):
+    F = per_cu * cus()
+    mix = B.MixedDecoder([make(B, n, precision=prec) for n in names])
+    assert mix.running_kernel(F) == "rowpar" and mix.running_kernel(F + 1) == past
+    g = torch.Generator(device="cuda")
+    g.manual_seed(per_cu)
+    llr = 2.0 + 2.5 * torch.randn((F + 1, mix.ld), generator=g, device="cuda")
+    if prec:
+        llr = torch.clamp(torch.round(4.0 * llr), -127, 127).to(torch.int8)
+    idx = torch.randint(0, len(names) + 1, (F + 1,), generator=g, device="cuda").to(torch.uint8)  # some name no code
+    d_o = torch.randint(0, 21, (F + 1,), generator=g, device="cuda").to(torch.uint8)
+    a = mix.decode(idx[:F].contiguous(), llr[:F].contiguous(), d_o[:F].contiguous())
+    b = mix.decode(idx, llr, d_o)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        assert torch.equal(x, y[:F])
