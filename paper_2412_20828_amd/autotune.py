@@ -10,8 +10,10 @@ and the argmin cached per (code, rows of H_o, I_m); tuned_alpha() returns it
 (0.75 when nothing is cached).
 
 Launch-shape knobs:
-  - frames per wave of the fixed-point decoders: 64 (integers held in 32-bit
-    registers) or 128 (the packed 16-bit kernels, two frames per lane);
+  - layout of the fixed-point decoders: the library's choice by call size
+    (row-parallel, matrix-core, 32-bit and packed kernels), or always the packed
+    16-bit kernels (128 frames per wave, two per lane), which exclude the
+    others;
   - waves per CU of the persistent grid.
 The tuner times every candidate on a synthetic batch of the decoder's own
 code at a given Eb/N0, at the size of the benchmark's decode calls, and keeps
@@ -63,13 +65,13 @@ def apply_cached(decoder, code_name: str, rows: int) -> bool:
 
 def tuned_decoder(code, pcm, code_name: str, rows: int, n_branches=9, mode=None, alpha=0.75, max_iter=8,
                   precision=0, flags=0):
-    """A decoder with the cached layout (packed or not) and grid; the
-    defaults when nothing is cached."""
+    """A decoder with the cached layout (always packed, or the library's choice
+    by call size) and grid; the defaults when nothing is cached."""
     from . import binding as B
     mode = B.MODE_RESTART if mode is None else mode
     entry = load().get(key(code_name, rows, precision, n_branches, _gpu_name()))
-    if entry and precision == B.FIX8:
-        flags |= B.PACKED16 if entry.get("packed16") else B.UNPACKED16
+    if entry and precision == B.FIX8 and entry.get("packed16"):
+        flags |= B.PACKED16
     dec = B.Decoder(code, pcm, n_branches=n_branches, mode=mode, alpha=alpha, max_iter=max_iter,
                     precision=precision, flags=flags)
     if entry and dec.specialized:
@@ -204,8 +206,13 @@ def tune(decoder, code_name: str, rows: int, ebn0: float = 3.0, frames: int = 0,
     for _ in range(2 * reps):
         decoder.decode_into(llr, d_o, bits, it, fl, workspace=ws)
     torch.cuda.synchronize()
+    # the grid belongs to the decoder's lane-per-frame kernel: where another runs
+    # at this size, only the default is a candidate
+    name = decoder.running_kernel(F)
+    own = name.startswith("spec_") and not name.endswith("_mm") and (
+        name.endswith("_pk16") == bool(decoder.flags & B.PACKED16))
     results = []
-    for wv in WAVES:
+    for wv in WAVES if own else [0]:
         decoder.set_tuning(wv)
         ws = torch.empty(max(1, decoder.workspace_size(F)), dtype=torch.uint8, device="cuda")
         decoder.decode_into(llr, d_o, bits, it, fl, workspace=ws)
@@ -232,24 +239,28 @@ def tune(decoder, code_name: str, rows: int, ebn0: float = 3.0, frames: int = 0,
 
 def tune_layout(code, pcm, code_name: str, rows: int, precision: int, ebn0: float = 3.0, frames: int = 0,
                 reps: int = 3, seed: int = 99, write: bool = True):
-    """Time every layout (fixed point: 64 or 128 frames per wave) and grid of
-    a nine-branch decoder; cache and return the best entry and every layout's
-    (best entry, timings)."""
+    """Time every layout (fixed point: the library's choice by call size, and
+    always packed where that is another kernel at this size) and grid of a
+    nine-branch decoder; cache and return the best entry and every layout's (best
+    entry, timings)."""
     from . import binding as B
-    cands = [B.UNPACKED16, B.PACKED16] if precision == B.FIX8 else [0]
+    cands = [0, B.PACKED16] if precision == B.FIX8 else [0]
+    frames = frames or default_frames(code.N)
     batch = None
     out = []
+    seen = set()
     for fl in cands:
         dec = B.Decoder(code, pcm, n_branches=9, max_iter=8, precision=precision, flags=fl)
-        if not dec.specialized:
+        if not dec.specialized or dec.running_kernel(frames) in seen:
             continue
+        seen.add(dec.running_kernel(frames))
         if batch is None:
-            batch = _batch(code_name, code.N, frames or default_frames(code.N), ebn0, seed)
+            batch = _batch(code_name, code.N, frames, ebn0, seed)
         out.append(tune(dec, code_name, rows, ebn0=ebn0, reps=reps, seed=seed, write=False, batch=batch))
     if not out:
         return None, out
     best = dict(max((b for b, _ in out), key=lambda b: b["frames_per_s"]))
-    best["default_frames_per_s"] = out[0][0]["default_frames_per_s"]  # the 64-frame layout, default grid
+    best["default_frames_per_s"] = out[0][0]["default_frames_per_s"]  # the library's choice, default grid
     if write:
         cache = load()
         cache[key(code_name, rows, precision, 9, _gpu_name())] = best
@@ -299,7 +310,7 @@ def main():
                 print("%s/%d/%s: no specialised kernel, skipped" % (name, rows, prec), flush=True)
                 continue
             print("%s/%d/%s: best %s, waves %d: %.1fM frames/s (default %.1fM)" % (
-                name, rows, prec, "128 frames per wave (packed)" if best["packed16"] else "64 frames per wave",
+                name, rows, prec, "always packed" if best["packed16"] else "layout by call size",
                 best["waves_per_cu"], best["frames_per_s"] / 1e6, best["default_frames_per_s"] / 1e6), flush=True)
 
 
