@@ -162,16 +162,12 @@ __device__ __forceinline__ uint2 search_row(const char *Eb, const StepWord *st, 
 template <int NK, bool FIX8>
 __device__ __forceinline__ uint2 row_record(const uint64_t *W, const uint4 &mk, uint2 u);
 
-// a posterior of the frame is NaN: its rows take ordered_row.  Every wave
-// holds the whole frame and finds the same
+// a posterior of the frame is NaN (past its end they are 1): its rows take
+// ordered_row.  Every wave holds the whole frame and finds the same
 template <int NK, bool FIX8>
-__device__ __forceinline__ bool has_nan(const float *y, const bool *in)
+__device__ __forceinline__ bool has_nan(const float *y)
 {
-    bool nan = false;
-#pragma unroll
-    for (int j = 0; j < NK; j++)
-        nan = nan || (in[j] && y[j] != y[j]);
-    return !FIX8 && __ballot(nan) != 0ull;
+    return !FIX8 && __builtin_amdgcn_ballot_w64(__builtin_isunordered(y[0], y[NK - 1])) != 0ull;
 }
 
 // the two least of a row by its columns mk of the type's input, k at E[k + 2 d_p]
@@ -330,7 +326,7 @@ __device__ __forceinline__ void decode_frame(const RowParArgs &A, const RowParTa
         type_input<NK, FIX8>(E, N, dp, lane, y, in, W, a);
         wave_order();
         // ---- 2. rows
-        if (has_nan<NK, FIX8>(y, in)) {
+        if (__builtin_expect(has_nan<NK, FIX8>(y), 0)) {
             for (int q = 0; q < tb.n_rounds; q++) {
                 const uint4 mk = tb.mask[q * WAVE + lane];
                 *reinterpret_cast<uint2 *>(Rb + tb.slot[q * WAVE + lane]) = ordered_row<NK, FIX8>(W, E, dp, mk);
@@ -517,7 +513,7 @@ __device__ __forceinline__ void decode_wide(const RowParArgs &A, const RowParTab
         type_input<NK, FIX8>(E, N, dp, lane, y, in, W, a);
         wave_order();
         // ---- 2. rows
-        if (has_nan<NK, FIX8>(y, in)) {
+        if (__builtin_expect(has_nan<NK, FIX8>(y), 0)) {
             if (na)
                 *reinterpret_cast<uint2 *>(Rb + slota) = ordered_row<NK, FIX8>(W, E, dp, mka);
             if (S2 && nb)
