@@ -217,8 +217,11 @@ __global__ void __launch_bounds__(WAVE) osd_kernel(OsdArgs A)
         float mx = fmaxf(r0, r1);
         for (int s = 1; s < WAVE; s <<= 1)
             mx = fmaxf(mx, __shfl_xor(mx, s));
-        const int sc = mx > 0.0f ? 14 - ilogbf(mx) : 0;  // every q below 2^15
-        const uint32_t q0 = (uint32_t)rintf(ldexpf(r0, sc)), q1 = (uint32_t)rintf(ldexpf(r1, sc));
+        // no scale holds an infinite reliability: pass 2 then takes every candidate
+        const bool finite = mx < __builtin_inff();
+        const int sc = finite && mx > 0.0f ? 14 - ilogbf(mx) : 0;  // every q below 2^15
+        const uint32_t q0 = finite ? (uint32_t)rintf(ldexpf(r0, sc)) : 0u;
+        const uint32_t q1 = finite ? (uint32_t)rintf(ldexpf(r1, sc)) : 0u;
         uint32_t pl[16][4];
 #pragma unroll
         for (int bp = 0; bp < 16; bp++) {
@@ -264,7 +267,7 @@ __global__ void __launch_bounds__(WAVE) osd_kernel(OsdArgs A)
             const uint32_t o = __shfl_xor(qmin, s);
             qmin = o < qmin ? o : qmin;
         }
-        const uint32_t thr = qmin + 128u;
+        const uint32_t thr = finite ? qmin + 128u : 0xffffffffu;
         // pass 2: exact FP64 cost of the candidates near the least
         double best = 0.0;
         int bkey = 0x7fffffff;
@@ -369,9 +372,11 @@ __global__ void __launch_bounds__(WAVE) osd_kernel(OsdArgs A)
 using i32x4 = __attribute__((__vector_size__(4 * sizeof(int)))) int;
 
 constexpr int Q_MAX = 32000;
-// doubled "reliability" of the rows past K.  A doubled cost stays below 2^21 in
-// magnitude ((64 + 4) Q_MAX) and below 2^23 with two of these added, so that it
-// fits beside an eight-bit index.
+// Doubled "reliability" of the rows past K.  A doubled cost of two real positions
+// is below 68 Q_MAX = 2,176,000 in magnitude (64 terms and two of 2 q), so with two
+// of these added it is below 2^23, and with an eight-bit index beside it below
+// 2^31.  A candidate with a pad costs Q_PAD more than the one without it, which is
+// a candidate of lower weight, so that no pad comes within the threshold.
 constexpr int Q_PAD = 1 << 21;
 
 struct DualLds {
