@@ -494,9 +494,9 @@ def run_serve(args):
                                "GPU (%d slots of %d frames, %s), OSD-2 for NMS failures %s"
                                % (len(tr), args.slots, args.slot_frames,
                                   "each step launched code by code" if args.serve_eager else
-                                  "each step one captured graph: one mixed-code kernel, then device OSD"
+                                  "each step one captured graph: one mixed-code call, then device OSD"
                                   if args.osd == "device" else "each step one captured graph of the mixed-code "
-                                  "kernel", "on the GPU" if args.osd == "device" else
+                                  "call", "on the GPU" if args.osd == "device" else
                                   "on %d host threads" % max(1, min(16, threads) - 2)),
                    "mean_request_frames": mean_frames},
         "saturation": sat,

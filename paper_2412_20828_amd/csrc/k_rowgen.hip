@@ -17,14 +17,20 @@
 //   3. lane = coordinate: the c2v of its rows over the branches in order, rows
 //      ascending, then y^(t).
 // The sums have the order of the one-lane-per-frame kernel (k_generic.hip), and
-// the results are the same bit for bit.  Message state lives in LDS; that
-// kernel moves every edge's message through device memory, runs a frame's
-// edges one after another and needs 64 frames to fill a wave.  It stays for
-// matrices whose records or state do not fit 64 KB of LDS (nine branches: from
-// about 890 rows in restart mode, 400 with edge memory) or 16-bit offsets.
+// the results are the same bit for bit, of posteriors that are infinite or NaN
+// too.  Message state lives in LDS; that kernel moves every edge's message
+// through device memory, runs a frame's edges one after another and needs 64
+// frames to fill a wave.  It stays for matrices whose records or state do not fit
+// 64 KB of LDS or 16-bit offsets (rowgen_stride bytes a row, shift and type:
+// nine branches from 874 rows (N = 127) or 892 (N = 63) in restart mode; extrinsic
+// messages from 437 or 446 with rows of up to 30 entries, 291 or 297 of up to 90;
+// literal memory 18 to 53 rows earlier; three branches with edge memory from
+// about 860 to 900 with rows of more than 30; one branch never) and for restart messages with an infinite or NaN alpha.
 //
-// What bounds it: VALU issue, as in k_rowpar.hip (3.7 and 7 instructions an
-// edge in steps 2 and 3 of restart mode, about 14 and 13 with edge memory).
+// What bounds it: VALU issue and LDS reads (3.7 and 7 vector instructions an
+// edge in steps 2 and 3 of restart mode, about 14 and 13 with edge memory;
+// counted: 0.55 instructions per CU-cycle and the LDS 31% busy on 20,000 frames of
+// (63,36) with 48 rows, 0.84 and 36% on 10,007 of plain (127,64)).
 // Measured at 3 dB, us a call, one-lane-per-frame kernel / this one:
 //   (63,36), 48 rows, 9 branches       1 frame 5415 / 35, 20,000: 14,705 / 224,
 //                                      200,000: 59,210 / 1,629

@@ -24,12 +24,13 @@
 // frame nor d_o, so frames need no bucketing and a call is one launch of one
 // workgroup per frame, handed out by the hardware as others end.  The sums are
 // formed in the order of the lane-per-frame kernels: the results are theirs
-// bit for bit.
+// bit for bit.  A frame with a NaN posterior searches its rows in their order too
+// (rowsearch.h).
 //
 // What bounds it: VALU issue.  An iteration of BCH(127,64) takes 2,900 VALU
 // instructions of a frame's three waves (6 per edge in step 3, 3.7 in step 2:
-// unpacking an address, the search), issued at 1.1 per CU-cycle with the LDS
-// 57% busy: 1.15-1.35 us per frame-iteration and CU, twice the lane-per-frame
+// unpacking an address, the search), issued at 1.0 per CU-cycle with the LDS
+// 51-59% busy: 1.15-1.35 us per frame-iteration and CU, twice the lane-per-frame
 // kernels' figure at full load, but from the first frame on.  One frame at
 // 3 dB: 39 us against 451 (decode_wide 25); 4,096 frames: 173 against 470; the mixed call of
 // 8,192 frames over four codes: 165 against 1,425.

@@ -27,17 +27,19 @@ frame depends only on that frame's LLRs and offset, and OSD is deterministic.
 With graph=True (the default) a slot's device work is also held as one HIP
 graph, captured once per slot when the engine starts: a mixed-code decode over
 the slot's whole capacity (frames past the batch carry a code index that names
-no decoder, so the prepass skips them; the engine's code set has a mixed-code
-kernel, so that is one prepass and one persistent kernel for every code of the
-batch) followed by the device OSD of the frames that did not converge.  A step
+no decoder and are skipped; up to 256 frames per CU, the default capacity, that is
+one launch of the row-parallel kernel, a frame per workgroup; for larger slots one
+prepass and the code set's mixed-code kernel) followed by the device OSD of the
+frames that did not converge.  A step
 of at least graph_min_frames frames replays it, with only the copies in and
 out, sized by the batch, enqueued beside the replay: one graph launch and
 three copies whatever the number of codes in the batch.  A smaller step (and
 every step with graph=False) decodes each code present by its own call on a
-stream of the slot's own: those calls pick the small-batch kernels, which
-spread a frame's nine branches over three waves and so finish a small batch
-about three times sooner than the one-wave mixed-code kernel.  The default
-limit, 128 frames per CU, is where the per-code calls leave those kernels.
+stream of the slot's own, on the row-parallel kernel too.  The replay saves
+launches and events and pays for a grid of the whole capacity; one burst of n
+frames over four codes, submission to results, ms, code by code / replay: 8,192
+frames 0.67 / 0.86, 32,768 1.48 / 1.63, 65,536 2.76 / 2.85.  The default limit is
+128 frames per CU.
 
 A slot uses 1 + (number of codes) streams (one with graph=True).  HIP maps a
 process's streams onto GPU_MAX_HW_QUEUES hardware queues (4 by default), and
